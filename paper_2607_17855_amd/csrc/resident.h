@@ -1,0 +1,16 @@
+// Register-resident agent kernels (resident.hip): plan and launch.
+#pragma once
+
+#include "internal.h"
+
+namespace bi {
+
+// launch_resident's answer for calls that it does not take.
+constexpr int kNoPlan = 1;
+
+// As launch_agent, for calls whose merged likelihood tensors fit in the
+// registers of a workgroup (else kNoPlan, nothing enqueued).
+int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
+                    const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream);
+
+}  // namespace bi

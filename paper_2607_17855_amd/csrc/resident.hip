@@ -1,0 +1,365 @@
+// Plan and launch of the register-resident agent kernels (resident_kernel.h).
+#include "resident.h"
+
+#include <algorithm>
+#include <cstring>
+
+#include "profile.h"
+#include "resident_kernel.h"
+
+namespace bi {
+
+namespace {
+
+using namespace res;
+
+constexpr size_t kLds = 160 * 1024;
+constexpr int kCus = 256;
+
+struct Plan {
+    Args a;
+    int shape = -1, threads = 0;
+    bool one = false;
+    size_t lds = 0;
+    double cost = 0.0;
+};
+
+// A group: factors of a maximal dependency list and the modalities inside it.
+struct GroupSet {
+    std::vector<int> fac, mods;
+};
+
+int div_up(int x, int y) { return (x + y - 1) / y; }
+int pad4(int x) { return (x + 3) & ~3; }
+
+// Modalities by falling rank, each into the first group that holds its list.
+std::vector<GroupSet> groups_of(const bi_model *m)
+{
+    std::vector<int> order(m->M);
+    for (int i = 0; i < m->M; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return m->mods[x].rank > m->mods[y].rank; });
+    std::vector<GroupSet> out;
+    for (int i : order) {
+        const int32_t *d = m->dep.data() + m->dep_off[i];
+        const int k = m->dep_off[i + 1] - m->dep_off[i];
+        GroupSet *in = nullptr;
+        for (GroupSet &g : out)
+            if (std::includes(g.fac.begin(), g.fac.end(), d, d + k)) {
+                in = &g;
+                break;
+            }
+        if (!in) {
+            out.push_back({std::vector<int>(d, d + k), {}});
+            in = &out.back();
+        }
+        in->mods.push_back(i);
+    }
+    return out;
+}
+
+// Element stride of factor f in a slice of modality md (0: not on its list).
+int stride_of(const ModDesc &md, int f)
+{
+    int s = 1;
+    for (int i = md.ncol - 1; i >= 0; --i) {
+        if (md.cf[i] == f) return s;
+        s *= md.cn[i];
+    }
+    s = md.Cp;
+    for (int i = md.nrow - 1; i >= 0; --i) {
+        if (md.rf[i] == f) return s;
+        s *= md.rn[i];
+    }
+    return 0;
+}
+
+// Everything that does not depend on the tile shape.
+bool plan_base(const bi_model *m, int algo, int T, Args &a, std::vector<GroupSet> &gs)
+{
+    if (m->F > kMaxF || m->M > kMaxM || !m->trivial_b) return false;
+    for (const FacDesc &fd : m->facs)
+        if (fd.n > kMaxN) return false;
+    gs = groups_of(m);
+    if ((int)gs.size() > kMaxG) return false;
+    for (const GroupSet &g : gs)
+        if (g.fac.size() > kRoles) return false;
+    std::memset(&a, 0, sizeof(a));
+    a.F = m->F;
+    a.M = m->M;
+    a.G = (int)gs.size();
+    a.shared = m->mb == 1;
+    a.T = T;
+    a.ntot = m->ntot;
+    int64_t bt = 0;
+    const int es = algo == BI_ALGO_VMP ? 8 : 4;
+    for (int f = 0; f < m->F; ++f) {
+        const FacDesc &fd = m->facs[f];
+        Fac &o = a.fac[f];
+        o.n = fd.n;
+        o.U = fd.U;
+        o.qo = fd.q_off;
+        o.b = fd.b_off;
+        o.lb = fd.lb_off;
+        o.ld = fd.ld_off;
+        o.b_agent = fd.b_agent;
+        o.ld_agent = fd.ld_agent;
+        // rows an odd number of 16-byte units apart: the lanes' 16-byte reads
+        // of consecutive rows fall on different banks
+        o.bs = pad4(fd.n);
+        if (o.bs * es / 16 % 2 == 0) o.bs += 16 / es;
+        o.bt = (int)bt;
+        bt += (int64_t)fd.U * fd.n * o.bs;
+        if (bt > (int64_t)kLds) return false;
+    }
+    a.btot = (int)((bt * es + 15) / 16 * 16 / es);
+    // state lanes: contexts side by side in a wave, or chunks of whole factors
+    a.nchunk = 1;
+    a.cpw = 64 / std::min(m->ntot, 64);
+    if (m->ntot > 64) {
+        a.cpw = 1;
+        a.nchunk = 0;
+        int start = 0, used = 0;
+        for (int f = 0; f < m->F; ++f) {
+            if (used + m->n[f] > 64) {
+                a.chunk0[a.nchunk++] = start;
+                start = a.fac[f].qo;
+                used = 0;
+            }
+            used += m->n[f];
+        }
+        a.chunk0[a.nchunk++] = start;
+        a.chunk0[a.nchunk] = m->ntot;
+    }
+    // 32-bit byte offsets into an agent's slices and soft tensors
+    for (const ModDesc &md : m->mods) {
+        a.llpc += md.slice;
+        if ((int64_t)md.K * md.slice * 8 > UINT32_MAX) return false;
+    }
+    return a.llpc * 8 * T <= (int64_t)UINT32_MAX;
+}
+
+// The roles of a group's factors on tiles of rb x cb: the assignment with the
+// least work per context (lanes, and values per line for the state phase).
+// role[r]: factor of role r, or -1.
+void choose_roles(const bi_model *m, const std::vector<int> &fac, int rb, int cb, int role[kRoles])
+{
+    const int k = (int)fac.size();
+    double best = -1.0;
+    std::vector<int> perm(fac);
+    std::sort(perm.begin(), perm.end());
+    do {
+        // rank 1: b1; 2: a1 b1; 3: a1 b0 b1; 4: all
+        int r[kRoles] = {-1, -1, -1, -1};
+        r[kB1] = perm[0];
+        if (k > 1) r[kA1] = perm[1];
+        if (k > 2) r[kB0] = perm[2];
+        if (k > 3) r[kA0] = perm[3];
+        auto n = [&](int i) { return r[i] < 0 ? 1 : m->n[r[i]]; };
+        const int na = div_up(n(kA1), rb), nb = div_up(n(kB1), cb), outer = n(kA0) * n(kB0);
+        const double lanes = (double)outer * na * nb;
+        double line = 0.0;
+        for (int i = 0; i < kRoles; ++i)
+            if (r[i] >= 0) {
+                const double len = i == kA1 ? (double)outer * nb : i == kB1 ? (double)outer * na : lanes / n(i);
+                line = std::max(line, len);
+            }
+        const double c = lanes * (2 * rb * cb + 4 * (rb + cb) + 20) / 64 + 2.0 * line;
+        if (best < 0.0 || c < best) {
+            best = c;
+            std::copy(r, r + kRoles, role);
+        }
+    } while (std::next_permutation(perm.begin(), perm.end()));
+}
+
+bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, const std::vector<GroupSet> &gs,
+                int shape, Plan &out)
+{
+    const int rb = kShapes[shape].rb, cb = kShapes[shape].cb;
+    out.a = base;
+    Args &a = out.a;
+    const bool fpi = algo == BI_ALGO_FPI;
+    const int contexts = fpi ? 1 : T, maxthreads = max_threads(rb, cb, fpi);
+    int role[kMaxG][kRoles];
+    int room[kMaxF];   // marginals of a factor that a tile may read (its states and padding)
+    for (int f = 0; f < a.F; ++f) room[f] = pad4(a.fac[f].n);
+    int64_t lanes = 0;
+    for (int gi = 0; gi < a.G; ++gi) {
+        choose_roles(m, gs[gi].fac, rb, cb, role[gi]);
+        Group &g = a.grp[gi];
+        for (int r = 0; r < kRoles; ++r) g.n[r] = role[gi][r] < 0 ? 1 : m->n[role[gi][r]];
+        g.na = div_up(g.n[kA1], rb);
+        g.nb = div_up(g.n[kB1], cb);
+        g.lane0 = (int)lanes;
+        lanes += (int64_t)g.n[kA0] * g.na * g.n[kB0] * g.nb;
+        if (lanes * contexts > maxthreads) return false;
+        if (role[gi][kA1] >= 0) room[role[gi][kA1]] = std::max(room[role[gi][kA1]], pad4(g.na * rb));
+        room[role[gi][kB1]] = std::max(room[role[gi][kB1]], pad4(g.nb * cb));
+    }
+    a.LT = (int)lanes;
+    // marginals of a context; the states' lines.  Values of a group in a line:
+    // one from every lane of the same state.  A tile's rows and columns past
+    // the last state write into lines behind it (pad), which nothing reads; the
+    // shares for an absent role go to the spare line at the end.
+    a.pq = std::max(kFirst, pad4(rb));   // (an absent a1 reads rb values)
+    int64_t off = 0;
+    int longest = 0, pad[kMaxF] = {};
+    for (int gi = 0; gi < a.G; ++gi) {
+        const Group &g = a.grp[gi];
+        if (role[gi][kA1] >= 0) pad[role[gi][kA1]] = std::max(pad[role[gi][kA1]], g.na * rb - g.n[kA1]);
+        pad[role[gi][kB1]] = std::max(pad[role[gi][kB1]], g.nb * cb - g.n[kB1]);
+    }
+    for (int f = 0; f < a.F; ++f) {
+        Fac &fd = a.fac[f];
+        fd.po = a.pq;
+        a.pq += room[f];
+        fd.len = 0;
+        for (int gi = 0; gi < a.G; ++gi) {
+            Group &g = a.grp[gi];
+            const int all = g.n[kA0] * g.na * g.n[kB0] * g.nb;
+            for (int r = 0; r < kRoles; ++r)
+                if (role[gi][r] == f) {
+                    g.q[r] = fd.po;
+                    g.line[r] = (int)off + fd.len;   // (base added below: off is the factor's first line)
+                    fd.len += r == kA1 ? all / g.na : r == kB1 ? all / g.nb : all / g.n[r];
+                }
+        }
+        fd.line = (int)off;
+        // lines of whole groups of 4 values, an odd number of 16-byte units apart
+        // (a factor on no list has none)
+        fd.pitch = fd.len ? pad4(fd.len) + 2 : 0;
+        off += (int64_t)(fd.n + pad[f]) * fd.pitch;
+        longest = std::max(longest, fd.len);
+        if (off > (int64_t)kLds / 8 || fd.len > 0x7fff) return false;
+    }
+    const int spare = (int)off;
+    a.pl = spare + 2 * rb;   // (an absent a1 writes rb values)
+    a.pl = (a.pl + 1) / 2 * 2;
+    for (int gi = 0; gi < a.G; ++gi) {
+        Group &g = a.grp[gi];
+        for (int r = 0; r < kRoles; ++r) {
+            const int f = role[gi][r];
+            g.pitch[r] = f < 0 ? (r == kA1 ? 1 : 0) : a.fac[f].pitch;
+            if (f < 0) {
+                g.q[r] = 0;
+                g.line[r] = spare;
+            }
+        }
+        g.m0 = gi ? a.grp[gi - 1].m1 : 0;
+        g.m1 = g.m0;
+        for (int i : gs[gi].mods) {
+            const ModDesc &md = m->mods[i];
+            Mod &o = a.mod[g.m1++];
+            o.la = md.la_off;
+            o.la_agent = md.la_agent;
+            o.ll = 0;
+            for (int k = 0; k < i; ++k) o.ll += m->mods[k].slice;
+            o.slice = md.slice;
+            o.m = i;
+            for (int r = 0; r < kRoles; ++r) o.s[r] = role[gi][r] < 0 ? 0 : stride_of(md, role[gi][r]);
+        }
+    }
+    if (a.pl > 0x7fff || a.pq > 0x7fff || T > 0x7fff) return false;   // (packed offsets, see State)
+    a.sv = a.cpw * a.pq;
+    const int cw = div_up(a.LT * contexts, 64);
+    const int units = a.nchunk == 1 ? div_up(contexts, a.cpw) : contexts * a.nchunk;
+    const int waves = fpi ? std::max(cw, units) : std::max(cw, std::min(units, maxthreads / 64));
+    if (waves * 64 > maxthreads) return false;
+    out.one = units <= waves;
+    out.threads = 64 * waves;
+    a.units = units;
+    // LDS, in doubles
+    const int64_t es = algo == BI_ALGO_VMP ? 8 : 4;
+    int64_t o = 0;
+    auto take = [&](int64_t n) {
+        const int64_t at = o;
+        o += (n + 1) / 2 * 2;
+        return (int)at;
+    };
+    a.o_q = take((fpi ? 2 : 2 * (int64_t)T) * a.pq);
+    a.o_p = take((int64_t)contexts * a.pl);
+    a.o_v = take((int64_t)waves * a.sv);
+    a.o_e = take((int64_t)waves * a.sv);
+    a.o_a = take(((int64_t)(T - 1) * a.F + (int64_t)T * a.M + 1) / 2);
+    a.o_f = take(fpi ? 0 : a.pq);
+    a.o_r = take(fpi || out.one ? 0 : 3 * 64 * (int64_t)units);
+    if (o * 8 > (int64_t)kLds) return false;
+    // the transition tables take the form that fits behind the rest
+    a.tab = kGlobal;
+    if (!fpi && T > 1) {
+        const int64_t room = (int64_t)kLds / 8 - o, once = ((int64_t)a.btot * es + 7) / 8;
+        a.tab = 2 * once <= room ? kBoth : once <= room ? kOnce : kGlobal;
+        a.o_b = take(a.tab == kBoth ? 2 * once : a.tab == kOnce ? once : 0);
+        if (a.tab == kGlobal) {
+            if (m->bytes > (int64_t)UINT32_MAX) return false;   // 32-bit byte offsets from the packed buffer
+            for (int f = 0; f < a.F; ++f) {
+                Fac &fd = a.fac[f];
+                fd.bt = (int)((algo == BI_ALGO_VMP ? fd.lb : fd.b) / es);
+                fd.bs = fd.n;
+            }
+        }
+    }
+    if (o * 8 > (int64_t)kLds) return false;
+    out.lds = (size_t)o * 8;
+    out.shape = shape;
+    // Estimated cycles of a sweep.  A workgroup's instructions keep its compute
+    // unit busy for 5 / 4 cycles each (4 SIMDs, 4 cycles for a wave's fp64
+    // instruction, some of them idle), one wave's chain of them takes 10 each and
+    // the barriers and LDS round trips 1000; as many workgroups as fit share
+    // a compute unit.  On the shapes tried the order of the estimates is that
+    // of the measured times within 5% (8 x 6 states, 1024 agents, VMP: 4 x 2
+    // tiles 36 us, 1 x 1 59 us; 12 x 10 x 8 states, 4096 agents, MMP: 6 x 4
+    // tiles 1.11 ms, 12 x 4 1.26 ms, 12 x 5 1.48 ms).
+    const int nmax = *std::max_element(m->n.begin(), m->n.end()), p = rb * cb;
+    const double ic = 2.0 * p + 4.0 * (rb + cb) + 20.0;
+    const double is = 160.0 + 2.0 * longest + (fpi ? 0.0 : (a.tab == kBoth ? 5.0 : a.tab == kOnce ? 8.0 : 16.0) * nmax) + 2.0 * nmax;
+    const int regs = p <= 4 ? 80 : p <= 8 ? 96 : p <= 24 ? 128 : p <= 32 ? 200 : 256;
+    const int fit = std::max(1, std::min(4 * (512 / regs) / waves, (int)(kLds / out.lds)));
+    const int side = std::min(fit, div_up(b, kCus));   // workgroups side by side on a compute unit
+    const double issue = 1.25 * (cw * ic + units * is) * (p > 48 ? 1.2 : 1.0);   // (the largest tiles spill)
+    const double chain = 10.0 * (ic + div_up(units, waves) * is) + 1000.0;
+    out.cost = std::max(side * issue, chain) * div_up(b, kCus * side);
+    return true;
+}
+
+bool make_plan(const bi_model *m, int algo, int b, int T, Plan &best)
+{
+    Args base;
+    std::vector<GroupSet> gs;
+    if (!plan_base(m, algo, T, base, gs)) return false;
+    best.shape = -1;
+    Plan p;
+    for (int s = 0; s < kNumShapes; ++s)
+        if (plan_shape(m, algo, b, T, base, gs, s, p) && (best.shape < 0 || p.cost < best.cost)) best = p;
+    return best.shape >= 0;
+}
+
+}  // namespace
+
+int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
+                    const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
+{
+    Plan p;
+    if (!make_plan(m, algo, b, T, p)) return kNoPlan;
+    Args &a = p.a;
+    a.base = m->dev;
+    a.iters = iters;
+    a.obs = obs;
+    a.ll = ll;
+    a.act = act;
+    a.prior = prior;
+    a.tau = tau;
+    a.q = q;
+    const void *fn = algo == BI_ALGO_FPI ? fpi_kernel(p.shape)
+                     : algo == BI_ALGO_VMP ? vmp_kernel(p.shape, p.one)
+                                           : mmp_kernel(p.shape, p.one);
+    hipError_t e = func_max_lds(fn, (int)kLds);
+    if (e == hipSuccess) {
+        ProfScope ps(algo == BI_ALGO_FPI ? "agent_filter_tile" : "agent_window_tile", stream);
+        void *args[] = {&a};
+        e = hipLaunchKernel(fn, dim3(b), dim3(p.threads), args, p.lds, stream);
+    }
+    if (e != hipSuccess) return fail(BI_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
+    return BI_OK;
+}
+
+}  // namespace bi

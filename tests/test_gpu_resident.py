@@ -1,0 +1,119 @@
+"""Register-resident agent kernels against the oracle, at the sizes where their
+plan changes: every rank of a dependency list, one and several groups of
+lists, a factor on no list, factors of one state, states on either side of a
+tile's and a batch's edge, contexts side by side in a wave and factors spread
+over several waves, several passes over the states, and the three places of
+the transition tables (in LDS twice, once, in the packed buffer).
+
+All arithmetic is fp64 and the result fp32, so an output differs from the
+fp64 oracle by its own rounding (3e-8 at most for a probability) and by what
+the sweeps amplify of 1e-16: TOL leaves four roundings.
+"""
+import numpy as np
+import pytest
+
+from paper_2607_17855_amd import bi, synth
+import oracle
+from test_gpu_parity import check_invariants
+
+pytestmark = pytest.mark.gpu
+TOL = 1.2e-7
+
+CASES = {
+    # name: (n, U, K, deps, b, T, per_agent)
+    "rank1": ([4], [2], [3], [[0]], 1, 8, False),
+    "one_step": ([8, 6], [3, 1], [5, 7, 4], [[0, 1]] * 3, 9, 1, True),
+    "rank2_edges": ([9, 5], [2, 3], [4, 3], [[0, 1], [1]], 5, 7, True),
+    "rank3_subsets": ([12, 10, 8], [4, 2, 1], [6, 5, 4, 3], [[1], [0, 1], [0, 1, 2], [2]], 4, 20, True),
+    "rank4": ([5, 3, 4, 2], [1, 2, 1, 3], [4, 3], [[0, 1, 2, 3], [1, 3]], 3, 6, False),
+    "groups": ([7, 4, 6, 3], [2, 1, 2, 1], [5, 4, 3, 6], [[0, 1], [1, 2], [2, 3], [3]], 6, 5, False),
+    "no_list": ([6, 5, 3], [2, 2, 2], [4], [[0, 2]], 4, 9, False),
+    "one_state": ([1, 7, 1, 4], [1, 2, 1, 3], [3, 5], [[0, 1, 2, 3], [0, 2]], 5, 4, True),
+    "long_factor": ([64, 3], [1, 2], [4, 3], [[0, 1], [0]], 3, 5, False),
+    "chunks": ([33, 31, 30], [2, 1, 2], [3, 4], [[0, 1], [2]], 3, 4, False),
+    "many_steps": ([5, 4], [3, 2], [4, 3], [[0, 1], [0]], 2, 90, True),
+    "tables_once": ([26, 9], [5, 3], [3], [[1]], 3, 32, False),
+    "tables_global": ([32, 31, 5], [5, 5, 2], [4], [[0]], 2, 17, False),
+    "large_tile": ([22, 17, 9], [2, 1, 2], [4, 3], [[0, 1, 2], [0, 2]], 2, 3, False),
+}
+
+
+def _torch():
+    import torch
+    return torch
+
+
+def _dev(x):
+    return _torch().from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def _workload(name, iters=16):
+    n, U, K, deps, b, T, own = CASES[name]
+    rng = np.random.Generator(np.random.PCG64(2600 + list(CASES).index(name)))
+    model = synth.make_model(rng, n, U, K, deps, b if own else 1, 1.0, 1.0, uniform_D=False)
+    obs, act = synth.sample_sequences(rng, model, b, T)
+    return synth.Workload(name, ["fpi", "vmp", "mmp"], model, obs, act, iters), rng
+
+
+def _run(pm, algo, *args, **kw):
+    """The call's result, and that the tile kernels ran it."""
+    bi.bi_profile_begin()
+    q = (pm.infer_soft if kw.pop("soft", False) else pm.infer)(algo, *args, **kw)
+    _torch().cuda.synchronize()
+    names = set(bi.bi_profile_end()) - {"soft_ll"}
+    assert names == {"agent_filter_tile" if algo == "fpi" else "agent_window_tile"}, names
+    return q.cpu().numpy()
+
+
+@pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_resident_vs_oracle(name, algo):
+    w, rng = _workload(name)
+    print(f"[gpu] {name} {algo} b={w.b} T={w.T}", flush=True)
+    pm = bi.PackedModel(w.model)
+    try:
+        q = _run(pm, algo, _dev(w.obs), _dev(w.act), w.iters)
+        check_invariants(w, q)
+        err = float(np.abs(q - oracle.infer(algo, w.model, w.obs, w.act, w.iters)).max())
+        # a first-step prior with zeros, and a damped update
+        prior = synth.random_prior(rng, w.model.n, w.b, p_zero=0.3)
+        qp = _run(pm, algo, _dev(w.obs), _dev(w.act), 5, prior=_dev(prior), damping=0.6)
+        errp = float(np.abs(qp - oracle.infer(algo, w.model, w.obs, w.act, 5, prior=prior, damping=0.6)).max())
+        print(f"[gpu]   vs oracle {err:.3e}, prior and damping {errp:.3e}", flush=True)
+        assert err <= TOL and errp <= TOL
+    finally:
+        pm.close()
+
+
+@pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
+@pytest.mark.parametrize("name", ["rank3_subsets", "groups"])
+def test_resident_soft(name, algo):
+    w, rng = _workload(name)
+    print(f"[gpu] {name} soft {algo}", flush=True)
+    pm = bi.PackedModel(w.model)
+    try:
+        so = synth.soft_obs(rng, w.obs, w.model.K, confidence=0.5)
+        q = _run(pm, algo, _dev(so), _dev(w.act), w.iters, soft=True)
+        ref = oracle.infer_soft(algo, w.model, so.astype(np.float64), w.act, w.iters)
+        assert float(np.abs(q - ref).max()) <= TOL
+        one = _run(pm, algo, _dev(synth.one_hot_obs(w.obs, w.model.K)), _dev(w.act), w.iters, soft=True)
+        assert np.array_equal(one, _run(pm, algo, _dev(w.obs), _dev(w.act), w.iters))
+    finally:
+        pm.close()
+
+
+@pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
+def test_resident_wide_logs(algo):
+    """Exact zeros in A (logs of -36.8 beside ordinary ones) over several
+    modalities: the softmax spans 1e-60 and its shift is not this sweep's
+    maximum."""
+    rng = np.random.Generator(np.random.PCG64(2690))
+    model = synth.make_model(rng, [6, 5], [2, 2], [4] * 5, [[0, 1]] * 5, 8, 0.5, 0.5, sparsity=0.5, uniform_D=False)
+    obs, act = synth.sample_sequences(rng, model, 8, 6)
+    print(f"[gpu] wide logs {algo}", flush=True)
+    pm = bi.PackedModel(model)
+    try:
+        q = _run(pm, algo, _dev(obs), _dev(act), 4)
+        assert float(np.abs(q - oracle.infer(algo, model, obs, act, 4)).max()) <= TOL
+    finally:
+        pm.close()
