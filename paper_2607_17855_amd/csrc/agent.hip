@@ -1122,8 +1122,8 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     // model, 16 sweeps) they were 1.2 to 9 times faster than the kernels below,
     // in sum 260 -> 71 ms (FPI), 94 -> 52 ms (VMP), 97 -> 52 ms (MMP).  What is
     // left for the kernels below: windows whose merged tensors exceed a
-    // workgroup's registers, lists of more than four factors, general
-    // B-dependency lists, factors of more than 64 states.
+    // workgroup's registers, lists of more than four factors, B-dependency
+    // lists of more than two (VMP, MMP), factors of more than 64 states.
     const int rc = launch_resident(m, algo, b, T, obs, ll, act, prior, tau, iters, q, stream);
     if (rc != kNoPlan) return rc;
     AgentArgs a;

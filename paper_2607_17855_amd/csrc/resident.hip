@@ -5,6 +5,7 @@
 #include <cstring>
 
 #include "profile.h"
+#include "resident_coupled.h"
 #include "resident_kernel.h"
 
 namespace bi {
@@ -15,11 +16,12 @@ using namespace res;
 
 constexpr size_t kLds = 160 * 1024;
 constexpr int kCus = 256;
+static_assert(sizeof(CoupledArgs) <= 4096, "kernel arguments");
 
 struct Plan {
-    Args a;
+    CoupledArgs c;   // c.a: every kernel's arguments; the rest: general B-dependency lists
     int shape = -1, threads = 0;
-    bool one = false;
+    bool one = false, coupled = false;
     size_t lds = 0;
     double cost = 0.0;
 };
@@ -76,9 +78,12 @@ int stride_of(const ModDesc &md, int f)
 // Everything that does not depend on the tile shape.
 bool plan_base(const bi_model *m, int algo, int T, Args &a, std::vector<GroupSet> &gs)
 {
-    if (m->F > kMaxF || m->M > kMaxM || !m->trivial_b) return false;
-    for (const FacDesc &fd : m->facs)
+    if (m->F > kMaxF || m->M > kMaxM) return false;
+    for (const FacDesc &fd : m->facs) {
         if (fd.n > kMaxN) return false;
+        // the transition phase for general lists takes lists of up to two factors
+        if (!m->trivial_b && algo != BI_ALGO_FPI && T > 1 && fd.nbd > 2) return false;
+    }
     gs = groups_of(m);
     if ((int)gs.size() > kMaxG) return false;
     for (const GroupSet &g : gs)
@@ -171,17 +176,131 @@ void choose_roles(const bi_model *m, const std::vector<int> &fac, int rb, int cb
     } while (std::next_permutation(perm.begin(), perm.end()));
 }
 
+// Transition phase for general B-dependency lists (resident_coupled.h) in a
+// workgroup of `threads`.  Returns the wave instructions of a sweep's
+// transition phases.
+double plan_trans(const bi_model *m, int algo, int T, int threads, CoupledArgs &c)
+{
+    const Args &a = c.a;
+    const int es = algo == BI_ALGO_VMP ? 8 : 4;
+    int role[kMaxF][kTRoles];   // factor of the role; kNext: the next state i
+    constexpr int kNext = 100, kNone = -1;
+    int lanes = 0;
+    for (int j = 0; j < a.F; ++j) {
+        const FacDesc &fd = m->facs[j];
+        Trans &tr = c.tr[j];
+        std::vector<int> dim = {kNext};
+        for (int k = 0; k < fd.nbd; ++k) dim.push_back(fd.bd[k]);
+        auto n = [&](int d) { return d == kNone ? 1 : d == kNext ? fd.n : m->n[d]; };
+        // the roles with the fewest padded values
+        std::sort(dim.begin(), dim.end());
+        int64_t best = -1;
+        do {
+            const int r[kTRoles] = {dim.size() > 2 ? dim[2] : kNone, dim[0], dim[1]};
+            const int64_t v = (int64_t)n(r[kO]) * div_up(n(r[kA]), kTA) * div_up(n(r[kB]), kTB);
+            if (best < 0 || v < best) {
+                best = v;
+                std::copy(r, r + kTRoles, role[j]);
+            }
+        } while (std::next_permutation(dim.begin(), dim.end()));
+        for (int r = 0; r < kTRoles; ++r) tr.n[r] = n(role[j][r]);
+        tr.na = div_up(tr.n[kA], kTA);
+        tr.nb = div_up(tr.n[kB], kTB);
+        lanes += tr.na * tr.nb;
+    }
+    // spare threads divide the outer states
+    const int spare = std::max(1, threads / std::max(1, lanes * (T - 1)));
+    c.LP = 0;
+    int64_t bt = 0;
+    double work = 0.0;
+    for (int j = 0; j < a.F; ++j) {
+        Trans &tr = c.tr[j];
+        tr.per = div_up(tr.n[kO], std::min(spare, tr.n[kO]));
+        tr.parts = div_up(tr.n[kO], tr.per);
+        tr.lane0 = c.LP;
+        c.LP += tr.na * tr.nb * tr.parts;
+        work = std::max(work, tr.per * 45.0 + 50.0);
+        // strides of the packed table [u][i][list], and of the copy in LDS
+        const FacDesc &fd = m->facs[j];
+        tr.packed = algo == BI_ALGO_VMP ? fd.lb_off : fd.b_off;
+        tr.agent = fd.b_agent;
+        tr.i = fd.n * fd.bstates;
+        for (int r = 0; r < kTRoles; ++r) {
+            int s = role[j][r] == kNext ? fd.bstates : 0;
+            for (int k = 0, low = fd.bstates; k < fd.nbd; ++k) {
+                low /= fd.bdn[k];
+                if (role[j][r] == fd.bd[k]) s = low;
+            }
+            tr.s[r] = s;
+        }
+        tr.rs = kTB * tr.nb;   // (rows an odd number of 16-byte units apart)
+        if (tr.rs * es / 16 % 2 == 0) tr.rs += 16 / es;
+        tr.os = kTA * tr.na * tr.rs;
+        tr.us = tr.n[kO] * tr.os;
+        tr.tb = (int)bt;
+        bt = std::min<int64_t>(bt + (int64_t)fd.U * tr.us, kLds);
+    }
+    c.steps = std::max(1, std::min(T - 1, threads / c.LP));
+    c.a.btot = (int)bt;
+    // lines: per factor the forward message's shares, then each child's
+    int off = 0;
+    auto shares = [&](int j, int r) {
+        const Trans &tr = c.tr[j];
+        return r == kO ? tr.na * tr.nb : r == kA ? tr.nb * tr.parts : tr.na * tr.parts;
+    };
+    auto role_of = [&](int j, int f) { return (int)(std::find(role[j], role[j] + kTRoles, f) - role[j]); };
+    for (int f = 0; f < a.F; ++f) {
+        const FacDesc &fd = m->facs[f];
+        TFac &tf = c.tf[f];
+        tf.line = off;
+        tf.fwd = shares(f, role_of(f, kNext));
+        int len = (tf.fwd + 1) / 2 * 2;
+        tf.nch = fd.nch;
+        for (int k = 0; k < fd.nch; ++k) {
+            tf.off[k] = len;
+            tf.len[k] = shares(fd.ch[k], role_of(fd.ch[k], f));
+            len += (tf.len[k] + 1) / 2 * 2;
+        }
+        tf.pitch = len / 2 % 2 ? len : len + 2;
+        off += std::max(div_up(fd.n, kTA) * kTA, div_up(fd.n, kTB) * kTB) * tf.pitch;
+    }
+    c.plt = off;   // (even: the pitches are)
+    if (2 * (int64_t)off > 0x7fff) c.LP = INT32_MAX;   // (packed offsets, see Place)
+    for (int j = 0; j < a.F; ++j) {
+        Trans &tr = c.tr[j];
+        for (int r = 0; r < kTRoles; ++r) {
+            const int d = role[j][r], f = d == kNext ? j : d;
+            if (d == kNone) {
+                tr.q[r] = tr.line[r] = tr.pitch[r] = 0;
+                continue;
+            }
+            const TFac &tf = c.tf[f];
+            int at = 0;
+            if (d != kNext)
+                for (int k = 0; k < tf.nch; ++k)
+                    if (m->facs[f].ch[k] == j) at = tf.off[k];
+            // the next state's marginals and lines are those of step t + 1
+            tr.q[r] = a.fac[f].po + (d == kNext ? a.pq : 0);
+            tr.line[r] = tf.line + at + (d == kNext ? c.plt : 0);
+            tr.pitch[r] = tf.pitch;
+        }
+    }
+    return work * div_up(T - 1, c.steps) * threads / 64;
+}
+
 bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, const std::vector<GroupSet> &gs,
                 int shape, Plan &out)
 {
     const int rb = kShapes[shape].rb, cb = kShapes[shape].cb;
-    out.a = base;
-    Args &a = out.a;
+    Args &a = out.c.a;
+    a = base;
+    const bool coupled = !m->trivial_b && algo != BI_ALGO_FPI && T > 1;
+    out.coupled = coupled;
     const bool fpi = algo == BI_ALGO_FPI;
-    const int contexts = fpi ? 1 : T, maxthreads = max_threads(rb, cb, fpi);
+    const int contexts = fpi ? 1 : T, maxthreads = max_threads(rb, cb, fpi || coupled);
     int role[kMaxG][kRoles];
     int room[kMaxF];   // marginals of a factor that a tile may read (its states and padding)
-    for (int f = 0; f < a.F; ++f) room[f] = pad4(a.fac[f].n);
+    for (int f = 0; f < a.F; ++f) room[f] = pad4(coupled ? div_up(a.fac[f].n, kTA) * kTA : a.fac[f].n);
     int64_t lanes = 0;
     for (int gi = 0; gi < a.G; ++gi) {
         choose_roles(m, gs[gi].fac, rb, cb, role[gi]);
@@ -269,6 +388,9 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
     a.units = units;
     // LDS, in doubles
     const int64_t es = algo == BI_ALGO_VMP ? 8 : 4;
+    double trans = 0.0;
+    if (coupled) trans = plan_trans(m, algo, T, out.threads, out.c);
+    if (coupled && out.c.LP > out.threads) return false;
     int64_t o = 0;
     auto take = [&](int64_t n) {
         const int64_t at = o;
@@ -276,8 +398,7 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
         return (int)at;
     };
     a.o_q = take((fpi ? 2 : 2 * (int64_t)T) * a.pq);
-    a.o_p = take((int64_t)contexts * a.pl);
-    a.o_v = take((int64_t)waves * a.sv);
+    a.o_p = take((int64_t)contexts * std::max(a.pl, coupled ? out.c.plt : 0));
     a.o_e = take((int64_t)waves * a.sv);
     a.o_a = take(((int64_t)(T - 1) * a.F + (int64_t)T * a.M + 1) / 2);
     a.o_f = take(fpi ? 0 : a.pq);
@@ -285,7 +406,15 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
     if (o * 8 > (int64_t)kLds) return false;
     // the transition tables take the form that fits behind the rest
     a.tab = kGlobal;
-    if (!fpi && T > 1) {
+    if (coupled) {
+        out.c.o_x = take((int64_t)a.F * sizeof(TFac) / 8);
+        out.c.o_s = take(out.one ? 0 : 2 * 64 * (int64_t)units);
+        const int64_t once = ((int64_t)a.btot * es + 7) / 8;
+        out.c.lds_tab = (o + once) * 8 <= (int64_t)kLds;
+        if (!mmp_coupled(shape, out.one, out.c.lds_tab)) return false;
+        a.o_b = take(out.c.lds_tab ? once : 0);
+        for (int f = 0; f < a.F; ++f) a.fac[f].bt = a.fac[f].bs = 0;
+    } else if (!fpi && T > 1) {
         const int64_t room = (int64_t)kLds / 8 - o, once = ((int64_t)a.btot * es + 7) / 8;
         a.tab = 2 * once <= room ? kBoth : once <= room ? kOnce : kGlobal;
         a.o_b = take(a.tab == kBoth ? 2 * once : a.tab == kOnce ? once : 0);
@@ -315,8 +444,8 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
     const int regs = p <= 4 ? 80 : p <= 8 ? 96 : p <= 24 ? 128 : p <= 32 ? 200 : 256;
     const int fit = std::max(1, std::min(4 * (512 / regs) / waves, (int)(kLds / out.lds)));
     const int side = std::min(fit, div_up(b, kCus));   // workgroups side by side on a compute unit
-    const double issue = 1.25 * (cw * ic + units * is) * (p > 48 ? 1.2 : 1.0);   // (the largest tiles spill)
-    const double chain = 10.0 * (ic + div_up(units, waves) * is) + 1000.0;
+    const double issue = 1.25 * (cw * ic + units * is + trans) * (p > 48 ? 1.2 : 1.0);   // (the largest tiles spill)
+    const double chain = 10.0 * (ic + div_up(units, waves) * is + trans / waves) + (coupled ? 2000.0 : 1000.0);
     out.cost = std::max(side * issue, chain) * div_up(b, kCus * side);
     return true;
 }
@@ -340,7 +469,7 @@ int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *ob
 {
     Plan p;
     if (!make_plan(m, algo, b, T, p)) return kNoPlan;
-    Args &a = p.a;
+    Args &a = p.c.a;
     a.base = m->dev;
     a.iters = iters;
     a.obs = obs;
@@ -349,13 +478,14 @@ int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *ob
     a.prior = prior;
     a.tau = tau;
     a.q = q;
-    const void *fn = algo == BI_ALGO_FPI ? fpi_kernel(p.shape)
-                     : algo == BI_ALGO_VMP ? vmp_kernel(p.shape, p.one)
-                                           : mmp_kernel(p.shape, p.one);
+    const bool fpi = algo == BI_ALGO_FPI;
+    const void *fn = fpi ? (m->trivial_b ? fpi_kernel(p.shape) : fpi_coupled(p.shape))
+                     : p.coupled ? (algo == BI_ALGO_VMP ? vmp_coupled(p.shape, p.one, p.c.lds_tab) : mmp_coupled(p.shape, p.one, p.c.lds_tab))
+                                 : (algo == BI_ALGO_VMP ? vmp_kernel(p.shape, p.one) : mmp_kernel(p.shape, p.one));
     hipError_t e = func_max_lds(fn, (int)kLds);
     if (e == hipSuccess) {
-        ProfScope ps(algo == BI_ALGO_FPI ? "agent_filter_tile" : "agent_window_tile", stream);
-        void *args[] = {&a};
+        ProfScope ps(fpi ? "agent_filter_tile" : "agent_window_tile", stream);
+        void *args[] = {p.coupled ? (void *)&p.c : (void *)&a};
         e = hipLaunchKernel(fn, dim3(b), dim3(p.threads), args, p.lds, stream);
     }
     if (e != hipSuccess) return fail(BI_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));

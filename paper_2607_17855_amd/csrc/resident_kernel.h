@@ -37,6 +37,7 @@
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
+#include "transition.h"
 
 namespace bi {
 namespace res {
@@ -51,8 +52,9 @@ constexpr int kFirst = 4;
 
 // Threads a workgroup may have: tiles of more than 24 values need more than the
 // 128 registers that 1024 threads leave each.
-// (the filter, whose next step's slices are in flight too: of 8)
-constexpr int max_threads(int rb, int cb, bool fpi) { return rb * cb >= (fpi ? 8 : 25) ? 512 : 1024; }
+// (more: the filter, whose next step's slices are in flight too, and the
+// kernel with a transition phase: of 8)
+constexpr int max_threads(int rb, int cb, bool more) { return rb * cb >= (more ? 8 : 25) ? 512 : 1024; }
 
 enum { kGlobal, kOnce, kBoth };
 
@@ -93,7 +95,7 @@ struct Args {
     // from the packed buffer, fac.bt counting elements from its start.
     int tab, btot;
     // LDS offsets in doubles: marginals, lines, softmax slots, transition tables, actions, first-step terms, roles
-    int o_q, o_p, o_v, o_e, o_b, o_a, o_f, o_r;
+    int o_q, o_p, o_e, o_b, o_a, o_f, o_r;
     const int32_t *obs;
     const double *ll;
     int64_t llpc;
@@ -290,17 +292,8 @@ __device__ inline void contract(const Tile &tl, const double (&x)[RB][CB], doubl
 // ---------------------------------------------------------------------------
 // states
 // ---------------------------------------------------------------------------
-// The larger of two values that are no signalling NaN (fmax quiets both
-// operands first, two more instructions).
-__device__ inline double max_of(double x, double y)
-{
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-    return r;
-}
-
-// Loops over n values, padded to whole groups of 4 (maxima: -inf, sums: 0):
-// two groups at a time, then one.
+// Loops over n values, padded to whole groups of 4 with zeros: two groups at a
+// time, then one.
 struct Four {
     double2 p, r;
     __device__ Four(const double *v)
@@ -308,18 +301,17 @@ struct Four {
     {
     }
     __device__ double sum() const { return (p.x + p.y) + (r.x + r.y); }
-    __device__ double max() const { return max_of(max_of(p.x, p.y), max_of(r.x, r.y)); }
 };
 
+// (maximum: what lies past the end is repeated, not read)
 __device__ inline double line_max(const double *v, int n)
 {
     double mx = -INFINITY;
-    int k = 0;
-    for (; k + 4 < n; k += 8) {
-        const Four f(v + k), g(v + k + 4);
-        mx = max_of(mx, max_of(f.max(), g.max()));
+    for (int k = 0; k < n; k += 4) {
+        const int l = n - 1;
+        const double x = v[k], y = v[min(k + 1, l)], z = v[min(k + 2, l)], w = v[min(k + 3, l)];
+        mx = fmax(fmax(mx, fmax(x, y)), fmax(z, w));
     }
-    if (k < n) mx = max_of(mx, Four(v + k).max());
     return mx;
 }
 
@@ -571,16 +563,17 @@ __device__ inline double softmax(const Args &a, double *smem, const State &st, i
                                  double &shift)
 {
     const int seg = base + st.po(), n = st.states();
-    double *vb = smem + a.o_v + seg, *eb = smem + a.o_e + seg;
+    double *eb = smem + a.o_e + seg;
     double e = exp_of(v - shift) * mult;
     if (st.on()) eb[st.s()] = e;
     wave_fence();
     double sum = line_sum(eb, n);
     wave_fence();
     if (__builtin_amdgcn_ballot_w64(!(sum > 1e-100 && sum < 1e100) && st.on())) {
-        if (st.on()) vb[st.s()] = v;
+        if (st.on()) eb[st.s()] = v;
         wave_fence();
-        shift = line_max(vb, n);
+        shift = line_max(eb, n);
+        wave_fence();
         e = exp_of(v - shift) * mult;
         if (st.on()) eb[st.s()] = e;
         wave_fence();
@@ -596,11 +589,7 @@ __device__ inline void init_lds(const Args &a, double *smem, int vectors, int wa
 {
     const int nt = (int)blockDim.x;
     for (int i = threadIdx.x; i < vectors * a.pq; i += nt) smem[a.o_q + i] = i % a.pq == 0 ? 1.0 : 0.0;
-    for (int i = a.o_p + (int)threadIdx.x; i < a.o_v; i += nt) smem[i] = 0.0;
-    for (int i = threadIdx.x; i < waves * a.sv; i += nt) {
-        smem[a.o_v + i] = -INFINITY;
-        smem[a.o_e + i] = 0.0;
-    }
+    for (int i = a.o_p + (int)threadIdx.x; i < a.o_e + waves * a.sv; i += nt) smem[i] = 0.0;   // (o_e follows o_p)
 }
 
 // Transition tables of the agent in LDS (Args::tab).
@@ -739,8 +728,9 @@ __global__ __launch_bounds__(max_threads(RB, CB, false)) void window_kernel(Args
 }
 
 // FPI: one step at a time, its merged tensor in registers for all its
-// iterations.  A wave per chunk of factors in the state phase.
-template <int RB, int CB>
+// iterations.  A wave per chunk of factors in the state phase.  TB: every
+// B-dependency list is {f}.
+template <int RB, int CB, bool TB>
 __global__ __launch_bounds__(max_threads(RB, CB, true)) void filter_kernel(Args a)
 {
     extern __shared__ double smem[];
@@ -809,26 +799,22 @@ __global__ __launch_bounds__(max_threads(RB, CB, true)) void filter_kernel(Args 
             const int n = st.states();
             if (t > 0) {
                 // (cur: the marginals of the step before)
-                const float *row = at<float>(a.base, row0 + acts[(t - 1) * a.F + f] * frow);
-                const double *qp = smem + cur + st.po();
                 double acc = 0.0;
-                int k = 0;
-                for (; k + 8 <= n; k += 8) {
-                    float b[8];
+                if constexpr (!TB) {   // the predictive marginal under the factorised marginals
+                    const FacDesc *facs = reinterpret_cast<const FacDesc *>(
+                        a.base + (sizeof(ModDesc) * a.M + kAlign - 1) / kAlign * kAlign);
+                    const FacDesc &fd = facs[f];
+                    BDep d = bdep_of(facs, fd);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) b[i] = row[k + i];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc = fma((double)b[i], qp[k + i], acc);
+                    for (int p = 0; p < kMaxBDep; ++p)
+                        for (int k = 0; k < a.F; ++k)
+                            if (p < d.k && fd.bd[p] == k) d.off[p] = a.fac[k].po;
+                    const float *B = at<float>(a.base, fd.b_off) + am * fd.b_agent;
+                    acc = bdep_row(d, B + ((int64_t)acts[(t - 1) * a.F + f] * n + st.s()) * d.bs, smem + cur, -1, 0);
+                } else {
+                    const float *row = at<float>(a.base, row0 + acts[(t - 1) * a.F + f] * frow);
+                    acc = plain_dot([&](int k) { return row[k]; }, smem + cur + st.po(), n);
                 }
-                if (k + 4 <= n) {
-                    float b[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) b[i] = row[k + i];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc = fma((double)b[i], qp[k + i], acc);
-                    k += 4;
-                }
-                for (; k < n; ++k) acc = fma((double)row[k], qp[k], acc);
                 mult = fmax(acc, kEps);
                 lp = 0.0;
             }
@@ -877,6 +863,7 @@ constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 // Kernels by shape (the files named above).
 const void *fpi_kernel(int shape);
+const void *fpi_coupled(int shape);   // general B-dependency lists
 const void *vmp_kernel(int shape, bool one);
 const void *mmp_kernel(int shape, bool one);
 

@@ -3,7 +3,9 @@ plan changes: every rank of a dependency list, one and several groups of
 lists, a factor on no list, factors of one state, states on either side of a
 tile's and a batch's edge, contexts side by side in a wave and factors spread
 over several waves, several passes over the states, and the three places of
-the transition tables (in LDS twice, once, in the packed buffer).
+the transition tables (in LDS twice, once, in the packed buffer); with
+general B-dependency lists, lists of one and two factors, with and without
+the factor itself, up to nine messages per state, tables in LDS and not.
 
 All arithmetic is fp64 and the result fp32, so an output differs from the
 fp64 oracle by its own rounding (3e-8 at most for a probability) and by what
@@ -37,6 +39,22 @@ CASES = {
     "large_tile": ([22, 17, 9], [2, 1, 2], [4, 3], [[0, 1, 2], [0, 2]], 2, 3, False),
 }
 
+# general B-dependency lists: (n, U, K, deps, lists, b, T, per_agent)
+COUPLED = {
+    "pairs": ([12, 10, 8], [4, 2, 1], [6, 5, 4, 3], [[1], [0, 1], [0, 1, 2], [2]], [[0, 1], [1, 2], [0, 2]], 3, 20, True),
+    "two_steps": ([5, 9], [2, 3], [4], [[0, 1]], [[0, 1], [0, 1]], 4, 2, False),
+    "not_itself": ([4, 7, 3], [1, 2, 2], [3, 4], [[0, 2], [1]], [[1], [0, 2], [2]], 5, 11, True),
+    # nine messages at factor 0 inside the window, one at the others
+    "children": ([3, 2, 4, 2, 3, 2, 2, 5], [2, 1, 1, 2, 1, 1, 2, 1], [4, 3], [[0, 2], [1, 7]],
+                 [[0]] + [[0, f] for f in range(1, 8)], 3, 5, False),
+    "one_state": ([1, 6, 5], [1, 2, 1], [3], [[0, 1, 2]], [[0, 1], [0, 1], [1, 2]], 4, 6, True),
+    "packed_tables": ([14, 13, 12], [5, 5, 4], [4], [[0, 1]], [[0, 1], [1, 2], [0, 2]], 2, 6, True),
+    "many_steps": ([4, 5], [3, 2], [4, 3], [[0, 1], [0]], [[0, 1], [1]], 2, 70, True),
+}
+# (FPI takes lists of any length)
+FILTER_LISTS = {"long_lists": ([4, 3, 2, 5], [1, 2, 2, 1], [3, 3], [[0, 1, 2, 3], [1, 3]],
+                               [[0, 1, 2, 3], [0, 2, 3], [2], [1, 3]], 5, 7, True)}
+
 
 def _torch():
     import torch
@@ -55,6 +73,14 @@ def _workload(name, iters=16):
     return synth.Workload(name, ["fpi", "vmp", "mmp"], model, obs, act, iters), rng
 
 
+def _coupled(name, iters=16):
+    n, U, K, deps, lists, b, T, own = {**COUPLED, **FILTER_LISTS}[name]
+    rng = np.random.Generator(np.random.PCG64(2650 + len(name)))
+    model = synth.make_model(rng, n, U, K, deps, b if own else 1, 1.0, 1.0, uniform_D=False, bdeps=lists)
+    obs, act = synth.sample_sequences(rng, model, b, T)
+    return synth.Workload(name, ["fpi", "vmp", "mmp"], model, obs, act, iters), rng
+
+
 def _run(pm, algo, *args, **kw):
     """The call's result, and that the tile kernels ran it."""
     bi.bi_profile_begin()
@@ -65,10 +91,7 @@ def _run(pm, algo, *args, **kw):
     return q.cpu().numpy()
 
 
-@pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
-@pytest.mark.parametrize("name", list(CASES))
-def test_resident_vs_oracle(name, algo):
-    w, rng = _workload(name)
+def _vs_oracle(name, algo, w, rng):
     print(f"[gpu] {name} {algo} b={w.b} T={w.T}", flush=True)
     pm = bi.PackedModel(w.model)
     try:
@@ -83,6 +106,17 @@ def test_resident_vs_oracle(name, algo):
         assert err <= TOL and errp <= TOL
     finally:
         pm.close()
+
+
+@pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_resident_vs_oracle(name, algo):
+    _vs_oracle(name, algo, *_workload(name))
+
+
+@pytest.mark.parametrize("name,algo", [(n, a) for n in COUPLED for a in ("fpi", "vmp", "mmp")] + [("long_lists", "fpi")])
+def test_resident_coupled(name, algo):
+    _vs_oracle(name, algo, *_coupled(name))
 
 
 @pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
