@@ -7,6 +7,7 @@
 #include "profile.h"
 #include "resident_coupled.h"
 #include "resident_kernel.h"
+#include "resident_streamed.h"
 
 namespace bi {
 
@@ -16,7 +17,7 @@ using namespace res;
 
 constexpr size_t kLds = 160 * 1024;
 constexpr int kCus = 256;
-static_assert(sizeof(CoupledArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(CoupledArgs) <= 4096 && sizeof(StreamedArgs) <= 4096, "kernel arguments");
 
 struct Plan {
     CoupledArgs c;   // c.a: every kernel's arguments; the rest: general B-dependency lists
@@ -76,7 +77,7 @@ int stride_of(const ModDesc &md, int f)
 }
 
 // Everything that does not depend on the tile shape.
-bool plan_base(const bi_model *m, int algo, int T, Args &a, std::vector<GroupSet> &gs)
+bool plan_base(const bi_model *m, int algo, int T, Args &a)
 {
     if (m->F > kMaxF || m->M > kMaxM) return false;
     for (const FacDesc &fd : m->facs) {
@@ -84,14 +85,11 @@ bool plan_base(const bi_model *m, int algo, int T, Args &a, std::vector<GroupSet
         // the transition phase for general lists takes lists of up to two factors
         if (!m->trivial_b && algo != BI_ALGO_FPI && T > 1 && fd.nbd > 2) return false;
     }
-    gs = groups_of(m);
-    if ((int)gs.size() > kMaxG) return false;
-    for (const GroupSet &g : gs)
-        if (g.fac.size() > kRoles) return false;
+    for (const ModDesc &md : m->mods)
+        if (md.rank > kRoles) return false;
     std::memset(&a, 0, sizeof(a));
     a.F = m->F;
     a.M = m->M;
-    a.G = (int)gs.size();
     a.shared = m->mb == 1;
     a.T = T;
     a.ntot = m->ntot;
@@ -174,6 +172,18 @@ void choose_roles(const bi_model *m, const std::vector<int> &fac, int rb, int cb
             std::copy(r, r + kRoles, role);
         }
     } while (std::next_permutation(perm.begin(), perm.end()));
+}
+
+// Transition tables read from the packed buffer, at 32-bit byte offsets.
+bool tables_in_place(const bi_model *m, int algo, Args &a)
+{
+    if (m->bytes > (int64_t)UINT32_MAX) return false;
+    for (int f = 0; f < a.F; ++f) {
+        Fac &fd = a.fac[f];
+        fd.bt = (int)(algo == BI_ALGO_VMP ? fd.lb / 8 : fd.b / 4);
+        fd.bs = fd.n;
+    }
+    return true;
 }
 
 // Transition phase for general B-dependency lists (resident_coupled.h) in a
@@ -417,15 +427,8 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
     } else if (!fpi && T > 1) {
         const int64_t room = (int64_t)kLds / 8 - o, once = ((int64_t)a.btot * es + 7) / 8;
         a.tab = 2 * once <= room ? kBoth : once <= room ? kOnce : kGlobal;
-        a.o_b = take(a.tab == kBoth ? 2 * once : a.tab == kOnce ? once : 0);
-        if (a.tab == kGlobal) {
-            if (m->bytes > (int64_t)UINT32_MAX) return false;   // 32-bit byte offsets from the packed buffer
-            for (int f = 0; f < a.F; ++f) {
-                Fac &fd = a.fac[f];
-                fd.bt = (int)((algo == BI_ALGO_VMP ? fd.lb : fd.b) / es);
-                fd.bs = fd.n;
-            }
-        }
+        a.o_b = take(a.tab * once);
+        if (a.tab == kGlobal && !tables_in_place(m, algo, a)) return false;
     }
     if (o * 8 > (int64_t)kLds) return false;
     out.lds = (size_t)o * 8;
@@ -453,13 +456,175 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
 bool make_plan(const bi_model *m, int algo, int b, int T, Plan &best)
 {
     Args base;
-    std::vector<GroupSet> gs;
-    if (!plan_base(m, algo, T, base, gs)) return false;
+    if (!plan_base(m, algo, T, base)) return false;
     best.shape = -1;
+    const std::vector<GroupSet> gs = groups_of(m);
+    base.G = (int)gs.size();
+    if (base.G > kMaxG) return false;
     Plan p;
     for (int s = 0; s < kNumShapes; ++s)
         if (plan_shape(m, algo, b, T, base, gs, s, p) && (best.shape < 0 || p.cost < best.cost)) best = p;
     return best.shape >= 0;
+}
+
+// Plan of the streamed window kernel for at most `blocks` blocks of a slice
+// per lane and step (resident_streamed.h).
+bool plan_streamed(const bi_model *m, int algo, int T, const Args &base, int blocks, int tab, StreamedArgs &c, size_t &lds,
+                   int &threads, double &cost)
+{
+    Args &a = c.a;
+    a = base;
+    int role[kStreamM][kSRoles];
+    int64_t lanes = 0, values = 0;
+    int longest = 0;   // blocks of a lane
+    for (int i = 0; i < a.M; ++i) {
+        const ModDesc &md = m->mods[i];
+        SMod &s = c.mod[i];
+        const int32_t *d = m->dep.data() + m->dep_off[i];
+        std::vector<int> rest(d, d + md.rank);
+        int *r = role[i];
+        std::fill(r, r + kSRoles, -1);
+        // columns: the factor with stride 1; where it has one or two states,
+        // and for the rows, the one that fills its blocks best; of the others
+        // the larger is divided among lanes.  (Windows of 256 agents, 16
+        // sweeps: 31 x 11 x 26 x 2 states with the last as columns 2.45 ms,
+        // with the third 1.54 ms; 30 x 30 x 19 x 3 1.56 ms, with the first
+        // 1.89 ms, as its loads then touch three times the lines.)
+        const int inner = md.cf[md.ncol - 1];
+        auto fills = [&](int x, int y) { return (int64_t)pad4(m->n[x]) * m->n[y] < (int64_t)pad4(m->n[y]) * m->n[x]; };
+        r[kCol] = m->n[inner] < 3 ? *std::min_element(rest.begin(), rest.end(), fills) : inner;
+        rest.erase(std::find(rest.begin(), rest.end(), r[kCol]));
+        auto pick = [&](auto better) {
+            if (rest.empty()) return -1;
+            const auto it = std::min_element(rest.begin(), rest.end(), better);
+            const int f = *it;
+            rest.erase(it);
+            return f;
+        };
+        r[kRow] = pick(fills);
+        r[kP] = pick([&](int x, int y) { return m->n[x] > m->n[y]; });
+        r[kO2] = pick([](int, int) { return false; });
+        for (int k = 0; k < kSRoles; ++k) {
+            s.n[k] = r[k] < 0 ? 1 : m->n[r[k]];
+            s.s[k] = r[k] < 0 ? 0 : stride_of(md, r[k]);
+        }
+        s.na = div_up(s.n[kRow], kBlk);
+        s.nb = div_up(s.n[kCol], kBlk);
+        s.per = std::min(s.n[kP], std::max(1, blocks / s.n[kO2]));
+        s.parts = div_up(s.n[kP], s.per);
+        s.lane0 = (int)lanes;
+        lanes += (int64_t)s.na * s.nb * s.parts;
+        if (lanes > kStreamThreads) return false;
+        longest = std::max(longest, s.per * s.n[kO2]);
+        values += md.slice;
+        s.slice = md.slice;
+        s.m = i;
+        s.la = md.la_off;
+        s.la_agent = md.la_agent;
+        s.ll = i ? c.mod[i - 1].ll + m->mods[i - 1].slice : 0;
+    }
+    c.LP = (int)lanes;
+    a.pq = kFirst;
+    int64_t off = 0;
+    for (int f = 0; f < a.F; ++f) {
+        Fac &fd = a.fac[f];
+        fd.po = a.pq;
+        a.pq += pad4(fd.n);
+        fd.line = (int)off;
+        fd.len = 0;
+        for (int i = 0; i < a.M; ++i) {
+            SMod &s = c.mod[i];
+            const int64_t blk = (int64_t)s.na * s.nb;
+            for (int k = 0; k < kSRoles; ++k)
+                if (role[i][k] == f) {
+                    s.q[k] = fd.po;
+                    s.line[k] = (int)off + fd.len;
+                    fd.len += (int)(k == kP ? blk : k == kO2 ? blk * s.parts : k == kRow ? s.nb * s.parts : s.na * s.parts);
+                }
+        }
+        fd.pitch = fd.len ? pad4(fd.len) + 2 : 0;
+        off += (int64_t)pad4(fd.n) * fd.pitch;
+        if (off > (int64_t)kLds / 8 || fd.len > 0x7fff) return false;
+    }
+    a.pl = (int)off + 2;   // (shares of absent roles go to the spare value behind the lines)
+    for (int i = 0; i < a.M; ++i)
+        for (int k = 0; k < kSRoles; ++k) {
+            SMod &s = c.mod[i];
+            s.pitch[k] = role[i][k] < 0 ? 0 : a.fac[role[i][k]].pitch;
+            if (role[i][k] < 0) {
+                s.q[k] = 0;
+                s.line[k] = (int)off;
+            }
+        }
+    if (a.pl > 0x7fff || T > 0x7fff) return false;   // (packed offsets, see State)
+    a.sv = a.cpw * a.pq;
+    a.units = a.nchunk == 1 ? div_up(T, a.cpw) : T * a.nchunk;
+    const int waves = std::min(kStreamThreads / 64, std::max(div_up((int)std::min<int64_t>(lanes * T, kStreamThreads), 64), a.units));
+    threads = 64 * waves;
+    c.steps = std::min(T, threads / c.LP);
+    if (c.steps < 1) return false;
+    int64_t o = 0;
+    auto take = [&](int64_t n) {
+        const int64_t at = o;
+        o += (n + 1) / 2 * 2;
+        return (int)at;
+    };
+    const int64_t once = T > 1 ? ((int64_t)a.btot * (algo == BI_ALGO_VMP ? 8 : 4) + 7) / 8 : 0;
+    const int64_t fixed = 2 * (int64_t)T * a.pq + (int64_t)waves * a.sv + ((int64_t)(T - 1) * a.F + (int64_t)T * a.M + 1) / 2 +
+                          a.pq + 3 * 64 * (int64_t)a.units + (int64_t)T * a.pq + 16;
+    a.tab = tab;
+    const int64_t room = (int64_t)kLds / 8 - fixed - a.tab * once;
+    c.chunk = (int)std::min<int64_t>(T, std::max<int64_t>(0, room / a.pl));
+    if (c.chunk < 1) return false;
+    c.steps = std::min(c.steps, c.chunk);
+    if (a.tab == kGlobal && T > 1 && !tables_in_place(m, algo, a)) return false;
+    a.o_q = take(2 * (int64_t)T * a.pq);
+    a.o_p = take((int64_t)c.chunk * a.pl);
+    a.o_e = take((int64_t)waves * a.sv);
+    a.o_a = take(((int64_t)(T - 1) * a.F + (int64_t)T * a.M + 1) / 2);
+    a.o_f = take(a.pq);
+    a.o_r = take(3 * 64 * (int64_t)a.units);
+    a.o_b = take(a.tab * once);
+    c.o_l = take((int64_t)T * a.pq);
+    if (o * 8 > (int64_t)kLds) return false;
+    lds = (size_t)o * 8;
+    // cycles of a sweep: the lanes' blocks (85 instructions each, 5 cycles on a
+    // SIMD's share of the waves) or the slices' way from L2, then the sums of the
+    // chunks' lines and their barriers, then the state phase, whose reads of a
+    // table outside LDS wait for one another (75 states, 20 steps, 1925 states'
+    // transitions: MMP 662 us with 9 steps to a chunk and the tables in memory)
+    const double rounds = (double)(T / c.chunk) * div_up(c.chunk, c.steps) +
+                          (T % c.chunk ? div_up(T % c.chunk, c.steps) : 0);
+    const double work = rounds * (longest * 85.0 + 100.0) * 5.0 * waves / 4.0;
+    int longest_line = 0;
+    for (int f = 0; f < a.F; ++f) longest_line = std::max(longest_line, a.fac[f].len);
+    const double sums = std::max(longest_line / 32.0 * 130.0, a.pl * (double)c.chunk / 16.0);
+    int n = 0;
+    for (int f = 0; f < a.F; ++f) n = std::max(n, a.fac[f].n);
+    const double states = T > 1 ? (double)div_up(a.units, waves) * n * (tab == kBoth ? 16.0 : tab == kOnce ? 30.0 : 400.0) : 0.0;
+    cost = std::max(work, (double)T * values * 8.0 / 64.0) + (800.0 + sums) * div_up(T, c.chunk) + states;
+    return true;
+}
+
+bool make_streamed(const bi_model *m, int algo, int T, StreamedArgs &best, size_t &lds, int &threads)
+{
+    Args base;
+    if (algo == BI_ALGO_FPI || !m->trivial_b || m->M > kStreamM || !plan_base(m, algo, T, base)) return false;
+    static const int kBlocks[] = {1, 2, 3, 4, 6, 8, 11, 16, 24, 32, 64, 128, 512, 4096};
+    double cost = -1.0;
+    StreamedArgs c;
+    for (int i = 0; i < 3 * (int)(sizeof(kBlocks) / sizeof(kBlocks[0])); ++i) {
+        const int blocks = kBlocks[i / 3], tab = kBoth - i % 3;
+        size_t l = 0;
+        int th = 0;
+        double co = 0.0;
+        if (!plan_streamed(m, algo, T, base, blocks, tab, c, l, th, co) || (cost >= 0.0 && co >= cost)) continue;
+        best = c;
+        lds = l;
+        threads = th;
+        cost = co;
+    }
+    return cost >= 0.0;
 }
 
 }  // namespace
@@ -468,24 +633,35 @@ int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *ob
                     const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
 {
     Plan p;
-    if (!make_plan(m, algo, b, T, p)) return kNoPlan;
-    Args &a = p.c.a;
-    a.base = m->dev;
-    a.iters = iters;
-    a.obs = obs;
-    a.ll = ll;
-    a.act = act;
-    a.prior = prior;
-    a.tau = tau;
-    a.q = q;
+    StreamedArgs sa;
     const bool fpi = algo == BI_ALGO_FPI;
-    const void *fn = fpi ? (m->trivial_b ? fpi_kernel(p.shape) : fpi_coupled(p.shape))
-                     : p.coupled ? (algo == BI_ALGO_VMP ? vmp_coupled(p.shape, p.one, p.c.lds_tab) : mmp_coupled(p.shape, p.one, p.c.lds_tab))
-                                 : (algo == BI_ALGO_VMP ? vmp_kernel(p.shape, p.one) : mmp_kernel(p.shape, p.one));
+    const void *fn;
+    void *args[1];
+    Args *a;
+    if (make_plan(m, algo, b, T, p)) {
+        a = &p.c.a;
+        args[0] = p.coupled ? (void *)&p.c : (void *)a;
+        fn = fpi ? (m->trivial_b ? fpi_kernel(p.shape) : fpi_coupled(p.shape))
+             : p.coupled ? (algo == BI_ALGO_VMP ? vmp_coupled(p.shape, p.one, p.c.lds_tab) : mmp_coupled(p.shape, p.one, p.c.lds_tab))
+                         : (algo == BI_ALGO_VMP ? vmp_kernel(p.shape, p.one) : mmp_kernel(p.shape, p.one));
+    } else if (make_streamed(m, algo, T, sa, p.lds, p.threads)) {
+        a = &sa.a;
+        args[0] = &sa;
+        fn = algo == BI_ALGO_VMP ? vmp_streamed() : mmp_streamed();
+    } else {
+        return kNoPlan;
+    }
+    a->base = m->dev;
+    a->iters = iters;
+    a->obs = obs;
+    a->ll = ll;
+    a->act = act;
+    a->prior = prior;
+    a->tau = tau;
+    a->q = q;
     hipError_t e = func_max_lds(fn, (int)kLds);
     if (e == hipSuccess) {
         ProfScope ps(fpi ? "agent_filter_tile" : "agent_window_tile", stream);
-        void *args[] = {p.coupled ? (void *)&p.c : (void *)&a};
         e = hipLaunchKernel(fn, dim3(b), dim3(p.threads), args, p.lds, stream);
     }
     if (e != hipSuccess) return fail(BI_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));

@@ -310,22 +310,13 @@ __global__ __launch_bounds__(max_threads(RB, CB, true)) void coupled_kernel(Coup
     const int agent = blockIdx.x, waves = (int)blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
     const int64_t am = a.shared ? 0 : agent;
-    int *acts = reinterpret_cast<int *>(smem + a.o_a), *obs = acts + (a.T - 1) * a.F;
-    if (!a.ll)
-        for (int i = threadIdx.x; i < a.T * a.M; i += blockDim.x) obs[i] = a.obs[(int64_t)agent * a.T * a.M + i];
-    for (int i = threadIdx.x; i < (a.T - 1) * a.F; i += blockDim.x)
-        acts[i] = a.act[(int64_t)agent * (a.T - 1) * a.F + i];
+    stage_window<BT>(a, smem, agent, am, ALGO == BI_ALGO_VMP, waves);   // (a.tab is kGlobal: no tables yet)
+    const int *acts = reinterpret_cast<const int *>(smem + a.o_a), *obs = acts + (a.T - 1) * a.F;
     int *tf = reinterpret_cast<int *>(smem + c.o_x);
     for (int i = threadIdx.x; i < (int)(a.F * sizeof(TFac) / 4); i += blockDim.x)
         tf[i] = reinterpret_cast<const int *>(c.tf)[i];
     BT *tab = reinterpret_cast<BT *>(smem + a.o_b);
-    init_lds(a, smem, 2 * a.T, waves);
     if (LT) stage_trans<BT>(c, am, a.btot, tab);
-    for (int f = 0; f < a.F; ++f)
-        for (int s = threadIdx.x; s < a.fac[f].n; s += blockDim.x)
-            smem[a.o_f + a.fac[f].po + s] =
-                a.prior ? fmax((double)a.prior[(int64_t)agent * a.ntot + a.fac[f].qo + s], kEps)
-                        : at<double>(a.base, a.fac[f].ld)[am * a.fac[f].ld_agent + s];
     Tile tl = tile_of<RB, CB>(a, a.T);
     Place pl = place_of(c);
     __syncthreads();
@@ -333,20 +324,13 @@ __global__ __launch_bounds__(max_threads(RB, CB, true)) void coupled_kernel(Coup
     if (tl.on) load_mod<RB, CB>(a, tl, a.mod[a.grp[tl.g].m0], obs, agent, tl.c, x);
     const int units = a.units;
     State one{};
-    int of = 0;
     double first_shift = __builtin_nan("");
     int2 *roles = reinterpret_cast<int2 *>(smem + a.o_r);
     for (int u = wave; u < units; u += waves) {
         const Where h = where_of(a, u, a.T);
         one = state_of(a, h, acts, a.T, am);
-        of = factor_of(a, h.j);
-        one.fwd = of;   // (the factor in place of the transition row)
-        if (!ONE) {
-            int2 *r = roles + 3 * (u * 64 + lane);
-            r[0] = make_int2(one.js, one.info);
-            r[1] = make_int2(one.tp, one.fwd);
-            r[2] = make_int2(0, __float_as_int((float)first_shift));
-        }
+        one.fwd = factor_of(a, h.j);   // (in place of the transition row)
+        if (!ONE) put_role(roles, u * 64 + lane, one);
         if (one.on()) smem[a.o_q + one.t() * a.pq + one.po() + one.s()] = 1.0 / one.states();   // uniform start
     }
     const int slots = wave * a.sv + (a.nchunk == 1 && lane < a.cpw * a.ntot ? lane / a.ntot * a.pq : 0);
@@ -359,10 +343,7 @@ __global__ __launch_bounds__(max_threads(RB, CB, true)) void coupled_kernel(Coup
             shift = first_shift;
             return one;
         }
-        const int2 *r = roles + 3 * (u * 64 + lane);
-        const int2 r0 = r[0], r1 = r[1], r2 = r[2];
-        shift = __int_as_float(r2.y);
-        return State{r0.x, r0.y, r1.x, r1.y, 0};
+        return get_role(roles, u * 64 + lane, shift);
     };
     for (int k = 0; k < a.iters; ++k) {
         pl.here();

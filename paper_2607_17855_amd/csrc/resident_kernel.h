@@ -613,6 +613,89 @@ __device__ inline void stage_tables(const Args &a, int64_t am, bool lb, BT *tab)
     }
 }
 
+// Outcomes, actions, transition tables and first-step terms in LDS.  First
+// step: log D is added to the message, the caller's prior (clamped) multiplies
+// the weight.
+template <class BT>
+__device__ inline void stage_window(const Args &a, double *smem, int agent, int64_t am, bool lb, int waves)
+{
+    int *acts = reinterpret_cast<int *>(smem + a.o_a), *obs = acts + (a.T - 1) * a.F;
+    if (!a.ll)
+        for (int i = threadIdx.x; i < a.T * a.M; i += blockDim.x) obs[i] = a.obs[(int64_t)agent * a.T * a.M + i];
+    for (int i = threadIdx.x; i < (a.T - 1) * a.F; i += blockDim.x)
+        acts[i] = a.act[(int64_t)agent * (a.T - 1) * a.F + i];
+    init_lds(a, smem, 2 * a.T, waves);
+    if (a.T > 1 && a.tab != kGlobal) stage_tables<BT>(a, am, lb, reinterpret_cast<BT *>(smem + a.o_b));
+    for (int f = 0; f < a.F; ++f)
+        for (int s = threadIdx.x; s < a.fac[f].n; s += blockDim.x)
+            smem[a.o_f + a.fac[f].po + s] =
+                a.prior ? fmax((double)a.prior[(int64_t)agent * a.ntot + a.fac[f].qo + s], kEps)
+                        : at<double>(a.base, a.fac[f].ld)[am * a.fac[f].ld_agent + s];
+}
+
+// A lane's roles in LDS: 5 words of State and the softmax shift (fp32: any
+// value near the maximum serves, as long as a factor's states share it).
+__device__ inline void put_role(int2 *roles, int i, const State &st)
+{
+    int2 *r = roles + 3 * i;
+    r[0] = make_int2(st.js, st.info);
+    r[1] = make_int2(st.tp, st.fwd);
+    r[2] = make_int2(st.bwd, __float_as_int(__builtin_nanf("")));
+}
+
+__device__ inline State get_role(const int2 *roles, int i, double &shift)
+{
+    const int2 *r = roles + 3 * i;
+    const int2 r0 = r[0], r1 = r[1], r2 = r[2];
+    shift = __int_as_float(r2.y);
+    return State{r0.x, r0.y, r1.x, r1.y, r2.x};
+}
+
+// The new marginal of a state, lam its likelihood message: transition messages
+// from the neighbouring steps, softmax.  Written to the other buffer, or in
+// the last sweep to the output.
+template <int ALGO, class BT>
+__device__ inline void update_state(const Args &a, double *smem, const BT *tab, const State &st, int agent, int unit,
+                                    int slots, int cur, int nxt, bool last, double lam, double &shift)
+{
+    double v = lam, mult = 1.0;
+    const int own = st.t() * a.pq + st.po();
+    const double *q = smem + cur + own;
+    const int n = st.states();
+    double fwd = 1.0, bwd = 1.0;   // MMP
+    if (st.prev()) {
+        const double d = forward<BT>(a, tab, st.fwd, q - a.pq, n);
+        if (ALGO == BI_ALGO_VMP)
+            v += d;
+        else
+            fwd = fmax(d, kEps);
+    } else {
+        const double d = smem[a.o_f + st.po() + st.s()];
+        if (a.prior)
+            (ALGO == BI_ALGO_VMP ? mult : fwd) = d;
+        else
+            v += ALGO == BI_ALGO_MMP && st.next() ? 0.5 * d : d;
+    }
+    if (st.next()) {
+        const double d = backward<BT>(a, tab, st.bwd, st.bs(), q + a.pq, n);
+        if (ALGO == BI_ALGO_VMP)
+            v += d;
+        else
+            bwd = fmax(d, kEps);
+    }
+    if (ALGO == BI_ALGO_MMP) mult = st.next() ? root(fwd * bwd) : fwd;
+    double qn = softmax(a, smem, st, slots, v, mult, shift);
+    if (st.on()) {
+        if (a.tau != 1.0) qn = (1.0 - a.tau) * q[st.s()] + a.tau * qn;
+        if (!last) {
+            smem[nxt + own + st.s()] = qn;
+        } else {
+            const Where h = where_of(a, unit, a.T);
+            a.q[((int64_t)agent * a.T + h.t) * a.ntot + h.j] = (float)qn;
+        }
+    }
+}
+
 // VMP and MMP.  ONE: every state has a lane (one pass of the state phase);
 // otherwise a lane's roles are kept in LDS.
 template <int ALGO, int RB, int CB, bool ONE>
@@ -625,21 +708,9 @@ __global__ __launch_bounds__(max_threads(RB, CB, false)) void window_kernel(Args
     const int64_t am = a.shared ? 0 : agent;
     // outcomes, actions and transition tables first, then, while the tiles'
     // loads are in flight, the roles of the state phase
-    int *acts = reinterpret_cast<int *>(smem + a.o_a), *obs = acts + (a.T - 1) * a.F;
-    if (!a.ll)
-        for (int i = threadIdx.x; i < a.T * a.M; i += blockDim.x) obs[i] = a.obs[(int64_t)agent * a.T * a.M + i];
-    for (int i = threadIdx.x; i < (a.T - 1) * a.F; i += blockDim.x)
-        acts[i] = a.act[(int64_t)agent * (a.T - 1) * a.F + i];
-    BT *tab = reinterpret_cast<BT *>(smem + a.o_b);
-    init_lds(a, smem, 2 * a.T, waves);
-    if (a.T > 1 && a.tab != kGlobal) stage_tables<BT>(a, am, ALGO == BI_ALGO_VMP, tab);
-    // first step: log D is added to the message, the caller's prior (clamped)
-    // multiplies the weight
-    for (int f = 0; f < a.F; ++f)
-        for (int s = threadIdx.x; s < a.fac[f].n; s += blockDim.x)
-            smem[a.o_f + a.fac[f].po + s] =
-                a.prior ? fmax((double)a.prior[(int64_t)agent * a.ntot + a.fac[f].qo + s], kEps)
-                        : at<double>(a.base, a.fac[f].ld)[am * a.fac[f].ld_agent + s];
+    stage_window<BT>(a, smem, agent, am, ALGO == BI_ALGO_VMP, waves);
+    const BT *tab = reinterpret_cast<const BT *>(smem + a.o_b);
+    const int *acts = reinterpret_cast<const int *>(smem + a.o_a), *obs = acts + (a.T - 1) * a.F;
     Tile tl = tile_of<RB, CB>(a, a.T);
     __syncthreads();
     double x[RB][CB];
@@ -647,17 +718,10 @@ __global__ __launch_bounds__(max_threads(RB, CB, false)) void window_kernel(Args
     const int units = a.units;
     State one{};
     double first_shift = __builtin_nan("");
-    // a lane's roles: 5 words of State and the softmax shift (fp32: any value
-    // near the maximum serves, as long as a factor's states share it)
     int2 *roles = reinterpret_cast<int2 *>(smem + a.o_r);
     for (int u = wave; u < units; u += waves) {
         one = state_of(a, where_of(a, u, a.T), acts, a.T, am);
-        if (!ONE) {
-            int2 *r = roles + 3 * (u * 64 + lane);
-            r[0] = make_int2(one.js, one.info);
-            r[1] = make_int2(one.tp, one.fwd);
-            r[2] = make_int2(one.bwd, __float_as_int((float)first_shift));
-        }
+        if (!ONE) put_role(roles, u * 64 + lane, one);
         if (one.on()) smem[a.o_q + one.t() * a.pq + one.po() + one.s()] = 1.0 / one.states();   // uniform start
     }
     const int slots = wave * a.sv + (a.nchunk == 1 && lane < a.cpw * a.ntot ? lane / a.ntot * a.pq : 0);
@@ -672,53 +736,14 @@ __global__ __launch_bounds__(max_threads(RB, CB, false)) void window_kernel(Args
         for (int u = wave; u < units; u += waves) {
             State st = one;
             double shift = first_shift;
-            if (!ONE) {
-                const int2 *r = roles + 3 * (u * 64 + lane);
-                const int2 r0 = r[0], r1 = r[1], r2 = r[2];
-                st = State{r0.x, r0.y, r1.x, r1.y, r2.x};
-                shift = __int_as_float(r2.y);
-            }
+            if (!ONE) st = get_role(roles, u * 64 + lane, shift);
             st.here();
-            double v = line_sum(smem + a.o_p + st.t() * a.pl + st.line(), st.len()), mult = 1.0;   // the likelihood message
-            const int own = st.t() * a.pq + st.po();
-            const double *q = smem + cur + own;
-            const int n = st.states();
-            double fwd = 1.0, bwd = 1.0;   // MMP
-            if (st.prev()) {
-                const double d = forward<BT>(a, tab, st.fwd, q - a.pq, n);
-                if (ALGO == BI_ALGO_VMP)
-                    v += d;
-                else
-                    fwd = fmax(d, kEps);
-            } else {
-                const double d = smem[a.o_f + st.po() + st.s()];
-                if (a.prior)
-                    (ALGO == BI_ALGO_VMP ? mult : fwd) = d;
-                else
-                    v += ALGO == BI_ALGO_MMP && st.next() ? 0.5 * d : d;
-            }
-            if (st.next()) {
-                const double d = backward<BT>(a, tab, st.bwd, st.bs(), q + a.pq, n);
-                if (ALGO == BI_ALGO_VMP)
-                    v += d;
-                else
-                    bwd = fmax(d, kEps);
-            }
-            if (ALGO == BI_ALGO_MMP) mult = st.next() ? root(fwd * bwd) : fwd;
-            double qn = softmax(a, smem, st, slots, v, mult, shift);
+            const double lam = line_sum(smem + a.o_p + st.t() * a.pl + st.line(), st.len());
+            update_state<ALGO, BT>(a, smem, tab, st, agent, u, slots, cur, nxt, k + 1 == a.iters, lam, shift);
             if (ONE)
                 first_shift = shift;
             else
                 roles[3 * (u * 64 + lane) + 2].y = __float_as_int((float)shift);
-            if (st.on()) {
-                if (a.tau != 1.0) qn = (1.0 - a.tau) * q[st.s()] + a.tau * qn;
-                if (k + 1 < a.iters) {
-                    smem[nxt + own + st.s()] = qn;
-                } else {
-                    const Where h = where_of(a, u, a.T);
-                    a.q[((int64_t)agent * a.T + h.t) * a.ntot + h.j] = (float)qn;
-                }
-            }
         }
         __syncthreads();
         const int tmp = cur;

@@ -55,6 +55,21 @@ COUPLED = {
 FILTER_LISTS = {"long_lists": ([4, 3, 2, 5], [1, 2, 2, 1], [3, 3], [[0, 1, 2, 3], [1, 3]],
                                [[0, 1, 2, 3], [0, 2, 3], [2], [1, 3]], 5, 7, True)}
 
+# windows that exceed the registers: slices streamed in 4 x 4 blocks.  Rows of
+# 1, 2, 3, 4 and 5 states, blocks that reach back, lists of one to four
+# factors, all steps at once and in chunks, the tables' three places, several
+# passes over the states
+STREAMED = {
+    "rank3": ([24, 21, 18], [2, 1, 2], [3, 2], [[0, 1, 2], [0, 2]], 3, 9, True),
+    "rank4_two_columns": ([31, 11, 26, 2], [2, 1, 1, 2], [2, 3, 4], [[0, 1, 2, 3], [1, 3], [3]], 2, 5, False),
+    "rank4_three_columns": ([17, 9, 13, 3], [1, 2, 1, 2], [2, 2, 3], [[0, 1, 2, 3], [3], [0, 2]], 2, 7, True),
+    "one_column": ([30, 27, 25, 1], [2, 2, 1, 1], [3], [[0, 1, 2, 3]], 2, 4, False),
+    "five_columns": ([32, 4, 21, 5], [1, 2, 2, 1], [2, 4], [[1, 2, 3], [0, 1, 2, 3]], 2, 6, False),
+    "streamed_steps": ([25, 32], [3, 2], [3, 4], [[0, 1], [1]], 2, 28, True),
+    "streamed_tables": ([32, 31, 30], [5, 5, 2], [2], [[0, 1, 2]], 2, 3, False),
+    "streamed_no_list": ([6, 32, 31, 29], [2, 1, 1, 2], [2], [[1, 2]], 3, 24, False),
+}
+
 
 def _torch():
     import torch
@@ -66,8 +81,8 @@ def _dev(x):
 
 
 def _workload(name, iters=16):
-    n, U, K, deps, b, T, own = CASES[name]
-    rng = np.random.Generator(np.random.PCG64(2600 + list(CASES).index(name)))
+    n, U, K, deps, b, T, own = {**CASES, **STREAMED}[name]
+    rng = np.random.Generator(np.random.PCG64(2600 + list({**CASES, **STREAMED}).index(name)))
     model = synth.make_model(rng, n, U, K, deps, b if own else 1, 1.0, 1.0, uniform_D=False)
     obs, act = synth.sample_sequences(rng, model, b, T)
     return synth.Workload(name, ["fpi", "vmp", "mmp"], model, obs, act, iters), rng
@@ -114,13 +129,19 @@ def test_resident_vs_oracle(name, algo):
     _vs_oracle(name, algo, *_workload(name))
 
 
+@pytest.mark.parametrize("algo", ["vmp", "mmp"])
+@pytest.mark.parametrize("name", list(STREAMED))
+def test_streamed_vs_oracle(name, algo):
+    _vs_oracle(name, algo, *_workload(name, iters=6))
+
+
 @pytest.mark.parametrize("name,algo", [(n, a) for n in COUPLED for a in ("fpi", "vmp", "mmp")] + [("long_lists", "fpi")])
 def test_resident_coupled(name, algo):
     _vs_oracle(name, algo, *_coupled(name))
 
 
-@pytest.mark.parametrize("algo", ["fpi", "vmp", "mmp"])
-@pytest.mark.parametrize("name", ["rank3_subsets", "groups"])
+@pytest.mark.parametrize("name,algo", [(n, a) for n in ("rank3_subsets", "groups") for a in ("fpi", "vmp", "mmp")]
+                         + [("rank4_three_columns", "vmp"), ("streamed_steps", "mmp")])
 def test_resident_soft(name, algo):
     w, rng = _workload(name)
     print(f"[gpu] {name} soft {algo}", flush=True)
