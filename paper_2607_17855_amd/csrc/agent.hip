@@ -1117,19 +1117,6 @@ constexpr bool kSegUpdate = BI_SEG_UPDATE;
 int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
                  const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
 {
-    // The register-resident kernels take every call that they have a plan for,
-    // the streamed one the other windows with trivial B-dependency lists: on
-    // 904 calls of sweep models (FPI, VMP and MMP, 256 agents sharing a model,
-    // 16 sweeps) they were 1.02 to 9 times faster than the kernels below, the
-    // resident ones in sum 260 -> 71 ms (FPI), 94 -> 52 ms (VMP), 97 -> 52 ms
-    // (MMP), the streamed one 100 -> 83 ms (VMP and MMP each; by time mostly
-    // one tensor that all agents read from beyond L2, 1.05 times, otherwise
-    // 1.1 to 4.3 times).  What is left for the kernels below: lists of more
-    // than four factors, B-dependency lists of more than two (VMP, MMP) or
-    // windows with such lists that exceed a workgroup, factors of more than 64
-    // states, and windows of more than eight modalities that exceed registers.
-    const int rc = launch_resident(m, algo, b, T, obs, ll, act, prior, tau, iters, q, stream);
-    if (rc != kNoPlan) return rc;
     AgentArgs a;
     a.base = m->dev;
     a.mods = reinterpret_cast<const ModDesc *>(m->dev);
@@ -1255,6 +1242,21 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     }
     if (a.nc < 1 || lds > kLdsMax)
         return fail(BI_ERR_UNSUPPORTED, "agent working set (%zu bytes of LDS) exceeds the 160 KB budget", lds);
+    // The register-resident kernels take every call that they have a plan for,
+    // the streamed one the other windows with trivial B-dependency lists: on
+    // 904 calls of sweep models (FPI, VMP and MMP, 256 agents sharing a model,
+    // 16 sweeps) they were 1.02 to 9 times faster than the kernels below, the
+    // resident ones in sum 260 -> 71 ms (FPI), 94 -> 52 ms (VMP), 97 -> 52 ms
+    // (MMP), the streamed one 100 -> 83 ms (VMP and MMP each; by time mostly
+    // one tensor that all agents read from beyond L2, 1.05 times, otherwise
+    // 1.1 to 4.3 times).  What is left for the kernels below: lists of more
+    // than four factors, B-dependency lists of more than two (VMP, MMP) or
+    // windows with such lists that exceed a workgroup, factors of more than 64
+    // states, and windows of more than eight modalities that exceed registers.
+    // (After the check above: windows too long for those kernels stay refused,
+    // whichever kernel would run them.)
+    const int rc = launch_resident(m, algo, b, T, obs, ll, act, prior, tau, iters, q, stream);
+    if (rc != kNoPlan) return rc;
     int src = a.tile ? kSrcTile : a.stage == kStageNone ? kSrcGlobal : kSrcLds;
     if (src == kSrcLds) {
         int longest = 0;

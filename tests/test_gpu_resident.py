@@ -172,3 +172,22 @@ def test_resident_wide_logs(algo):
         assert float(np.abs(q - oracle.infer(algo, model, obs, act, 4)).max()) <= TOL
     finally:
         pm.close()
+
+
+def test_longest_filter_window():
+    """The longest window that the agent-resident family takes, and the first
+    that it refuses (before any launch): 24 bytes per state and step."""
+    rng = np.random.Generator(np.random.PCG64(2691))
+    model = synth.make_model(rng, [8, 6], [3, 1], [5, 7, 4], [[0, 1]] * 3, 1, 1.0, 1.0, uniform_D=False)
+    obs, act = synth.sample_sequences(rng, model, 1, 500)
+    print("[gpu] fpi b=1 T=480, 500", flush=True)
+    pm = bi.PackedModel(model)
+    try:
+        o, u = np.ascontiguousarray(obs[:, :480]), np.ascontiguousarray(act[:, :479])
+        q = _run(pm, "fpi", _dev(o), _dev(u), 4)
+        assert float(np.abs(q - oracle.infer("fpi", model, o, u, 4)).max()) <= TOL
+        with pytest.raises(bi.BiError) as ei:
+            pm.infer("fpi", _dev(obs), _dev(act), 4)
+        assert ei.value.code == bi.BI_ERR_UNSUPPORTED
+    finally:
+        pm.close()
