@@ -423,7 +423,10 @@ void bi_free_model(bi_model *model);
  * every kernel the library enqueues is bracketed by a pair of HIP events on
  * the call's stream (the recording adds two small packets per launch).
  * bi_profile_end waits for those events and reports, per kernel class
- * ("lik", "update", "bucket", "init", "agent_window", "agent_filter"), the
+ * ("lik", "update", "bucket", "init", and one name per agent-resident kernel:
+ * "agent_window_resident", "agent_window_coupled", "agent_window_streamed",
+ * "agent_filter_resident" for the register-resident ones, "agent_window",
+ * "agent_window_tile", "agent_filter", "agent_filter_tile" for the others), the
  * number of launches and their summed duration in milliseconds, in at most
  * `cap` entries of `out`; *n_out receives the number of classes seen.
  * Process-wide; not for concurrent use from several threads.

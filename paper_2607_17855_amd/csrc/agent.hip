@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdio>
 
 #include "internal.h"
 #include "profile.h"
@@ -1111,31 +1112,19 @@ constexpr size_t kLdsMax = 160 * 1024;
 #endif
 constexpr bool kSegUpdate = BI_SEG_UPDATE;
 
-
-}  // namespace
-
-int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
-                 const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
+// The part of a call's plan that depends on shapes alone: a's counts, LDS
+// layout and forms, and the LDS bytes; an error code where the family refuses
+// the call.
+int plan_agent(const bi_model *m, int algo, int T, AgentArgs &a, size_t &lds)
 {
-    AgentArgs a;
-    a.base = m->dev;
-    a.mods = reinterpret_cast<const ModDesc *>(m->dev);
-    a.facs = reinterpret_cast<const FacDesc *>(m->dev + align_up((int64_t)sizeof(ModDesc) * m->M, kAlign));
     a.F = m->F;
     a.M = m->M;
     a.shared = m->mb == 1;
     a.T = T;
-    a.iters = iters;
     a.ntot = m->ntot;
     a.zvpc = m->zvpc;
-    a.obs = obs;
-    a.ll = ll;
     a.llpc = 0;
     for (const ModDesc &md : m->mods) a.llpc += md.slice;
-    a.act = act;
-    a.prior = prior;
-    a.tau = tau;
-    a.q = q;
     // lanes per (step, factor) segment of the window kernels' update: the
     // power of two covering the largest factor, up to a wave
     // (FPI: segments of every factor in one pass of the workgroup)
@@ -1180,7 +1169,7 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
         a.bdoubles = a.bst ? (int)((bytes + 7) / 8) : 0;
     }
     const size_t bt = 8 * (size_t)a.bdoubles;
-    size_t fixed, per_ctx = (size_t)m->zvpc * 8, lds;
+    size_t fixed, per_ctx = (size_t)m->zvpc * 8;
     a.stage = kStageNone;
     if (algo == BI_ALGO_FPI) {
         fixed = (3 * TN + m->ntot) * 8 + (size_t)m->ntot * 4 + per_ctx + bt;
@@ -1242,6 +1231,38 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     }
     if (a.nc < 1 || lds > kLdsMax)
         return fail(BI_ERR_UNSUPPORTED, "agent working set (%zu bytes of LDS) exceeds the 160 KB budget", lds);
+    return BI_OK;
+}
+
+// Where phase 1 of a planned window call reads the slices.
+int slice_src(const bi_model *m, const AgentArgs &a)
+{
+    int src = a.tile ? kSrcTile : a.stage == kStageNone ? kSrcGlobal : kSrcLds;
+    if (src == kSrcLds) {
+        int longest = 0;
+        for (const FacDesc &fd : m->facs) longest = std::max(longest, (int)fd.n);
+        for (const ModDesc &md : m->mods) longest = std::max(longest, (int)std::max(md.R, md.C));
+        if (longest <= 8) src = kSrcLdsShort;
+    }
+    return src;
+}
+
+// Profile name of a planned call's kernel.
+const char *class_name(int algo, const AgentArgs &a)
+{
+    return algo == BI_ALGO_FPI ? (a.tile ? "agent_filter_tile" : "agent_filter")
+                               : a.tile ? "agent_window_tile" : "agent_window";
+}
+
+}  // namespace
+
+int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
+                 const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
+{
+    AgentArgs a;
+    size_t lds = 0;
+    int rc = plan_agent(m, algo, T, a, lds);
+    if (rc != BI_OK) return rc;
     // The register-resident kernels take every call that they have a plan for,
     // the streamed one the other windows with trivial B-dependency lists: on
     // 904 calls of sweep models (FPI, VMP and MMP, 256 agents sharing a model,
@@ -1255,15 +1276,19 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     // states, and windows of more than eight modalities that exceed registers.
     // (After the check above: windows too long for those kernels stay refused,
     // whichever kernel would run them.)
-    const int rc = launch_resident(m, algo, b, T, obs, ll, act, prior, tau, iters, q, stream);
+    rc = launch_resident(m, algo, b, T, obs, ll, act, prior, tau, iters, q, stream);
     if (rc != kNoPlan) return rc;
-    int src = a.tile ? kSrcTile : a.stage == kStageNone ? kSrcGlobal : kSrcLds;
-    if (src == kSrcLds) {
-        int longest = 0;
-        for (const FacDesc &fd : m->facs) longest = std::max(longest, (int)fd.n);
-        for (const ModDesc &md : m->mods) longest = std::max(longest, (int)std::max(md.R, md.C));
-        if (longest <= 8) src = kSrcLdsShort;
-    }
+    a.base = m->dev;
+    a.mods = reinterpret_cast<const ModDesc *>(m->dev);
+    a.facs = reinterpret_cast<const FacDesc *>(m->dev + align_up((int64_t)sizeof(ModDesc) * m->M, kAlign));
+    a.iters = iters;
+    a.obs = obs;
+    a.ll = ll;
+    a.act = act;
+    a.prior = prior;
+    a.tau = tau;
+    a.q = q;
+    const int src = slice_src(m, a);
     const bool tb = m->trivial_b;
     // instantiation tables [src][tb][wide]; wide: some modality has a side of
     // more than two factors (the general side code is compiled only there)
@@ -1296,9 +1321,7 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
                                            : kMmp[src][tb][wide];
     hipError_t e = func_max_lds(fn, (int)kLdsMax);
     if (e == hipSuccess) {
-        ProfScope p(algo == BI_ALGO_FPI ? (a.tile ? "agent_filter_tile" : "agent_filter")
-                                    : a.tile ? "agent_window_tile" : "agent_window",
-                stream);
+        ProfScope p(class_name(algo, a), stream);
         void *args[] = {&a};
         e = hipLaunchKernel(fn, dim3(b), dim3(kThreads), args, lds, stream);
     }
@@ -1307,3 +1330,28 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
 }
 
 }  // namespace bi
+
+// The kernel that an agent-resident call of these shapes runs and its plan, as
+// text: its profile name, then what the tests need to tell its forms apart.
+// (For tests; not declared in bi.h.)
+extern "C" int bi_test_agent_plan(const bi_model *model, int32_t b, int32_t T, int32_t algo, char *buf, size_t cap)
+{
+    using namespace bi;
+    try {
+        if (!model || !buf || cap == 0 || b < 1 || T < 1 || algo < BI_ALGO_FPI || algo > BI_ALGO_MMP)
+            return fail(BI_ERR_INVALID_ARG, "invalid argument");
+        AgentArgs a;
+        size_t lds = 0;
+        const int rc = plan_agent(model, algo, T, a, lds);
+        if (rc != BI_OK) return rc;
+        if (describe_resident(model, algo, b, T, buf, cap)) return BI_OK;
+        static const char *srcs[] = {"lds", "global", "tile", "lds_short"};
+        std::snprintf(buf, cap, "%s src=%s chunk=%d tables=%s lds=%zu", class_name(algo, a),
+                      algo == BI_ALGO_FPI ? srcs[a.tile ? kSrcTile : a.stage == kStageNone ? kSrcGlobal : kSrcLds]
+                                          : srcs[slice_src(model, a)],
+                      a.nc, a.bst ? "lds" : "packed", lds);
+        return BI_OK;
+    } catch (...) {
+        return fail(BI_ERR_INVALID_ARG, "unexpected host exception");
+    }
+}

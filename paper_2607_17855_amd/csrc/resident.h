@@ -13,4 +13,7 @@ constexpr int kNoPlan = 1;
 int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
                     const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream);
 
+// The same choice as text (profile name of the kernel, its plan); false: no plan.
+bool describe_resident(const bi_model *m, int algo, int b, int T, char *buf, size_t cap);
+
 }  // namespace bi

@@ -2,6 +2,7 @@
 #include "resident.h"
 
 #include <algorithm>
+#include <cstdio>
 #include <cstring>
 
 #include "profile.h"
@@ -627,30 +628,64 @@ bool make_streamed(const bi_model *m, int algo, int T, StreamedArgs &best, size_
     return cost >= 0.0;
 }
 
+// The kernel and arguments of a call.
+struct Choice {
+    Plan p;           // (streamed: lds and threads of it)
+    StreamedArgs sa;
+    const void *fn;
+    const char *name;   // profile class
+    Args *a;
+    void *args;
+};
+
+bool choose(const bi_model *m, int algo, int b, int T, Choice &c)
+{
+    const bool fpi = algo == BI_ALGO_FPI, vmp = algo == BI_ALGO_VMP;
+    Plan &p = c.p;
+    if (make_plan(m, algo, b, T, p)) {
+        c.a = &p.c.a;
+        c.args = p.coupled ? (void *)&p.c : (void *)c.a;
+        c.fn = fpi ? (m->trivial_b ? fpi_kernel(p.shape) : fpi_coupled(p.shape))
+             : p.coupled ? (vmp ? vmp_coupled(p.shape, p.one, p.c.lds_tab) : mmp_coupled(p.shape, p.one, p.c.lds_tab))
+                         : (vmp ? vmp_kernel(p.shape, p.one) : mmp_kernel(p.shape, p.one));
+        c.name = fpi ? "agent_filter_resident" : p.coupled ? "agent_window_coupled" : "agent_window_resident";
+        return true;
+    }
+    if (make_streamed(m, algo, T, c.sa, p.lds, p.threads)) {
+        c.a = &c.sa.a;
+        c.args = &c.sa;
+        c.fn = vmp ? vmp_streamed() : mmp_streamed();
+        c.name = "agent_window_streamed";
+        return true;
+    }
+    return false;
+}
+
 }  // namespace
+
+bool describe_resident(const bi_model *m, int algo, int b, int T, char *buf, size_t cap)
+{
+    Choice c;
+    if (!choose(m, algo, b, T, c)) return false;
+    static const char *tabs[] = {"packed", "once", "twice"};
+    const Plan &p = c.p;
+    if (c.a == &c.sa.a)
+        std::snprintf(buf, cap, "%s chunk=%d steps=%d tables=%s threads=%d lds=%zu", c.name, c.sa.chunk, c.sa.steps,
+                      tabs[c.a->tab], p.threads, p.lds);
+    else
+        std::snprintf(buf, cap, "%s tile=%dx%d tables=%s passes=%s groups=%d threads=%d lds=%zu", c.name,
+                      kShapes[p.shape].rb, kShapes[p.shape].cb,
+                      p.coupled ? (p.c.lds_tab ? "lds" : "packed") : tabs[c.a->tab], p.one ? "one" : "several", c.a->G,
+                      p.threads, p.lds);
+    return true;
+}
 
 int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
                     const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
 {
-    Plan p;
-    StreamedArgs sa;
-    const bool fpi = algo == BI_ALGO_FPI;
-    const void *fn;
-    void *args[1];
-    Args *a;
-    if (make_plan(m, algo, b, T, p)) {
-        a = &p.c.a;
-        args[0] = p.coupled ? (void *)&p.c : (void *)a;
-        fn = fpi ? (m->trivial_b ? fpi_kernel(p.shape) : fpi_coupled(p.shape))
-             : p.coupled ? (algo == BI_ALGO_VMP ? vmp_coupled(p.shape, p.one, p.c.lds_tab) : mmp_coupled(p.shape, p.one, p.c.lds_tab))
-                         : (algo == BI_ALGO_VMP ? vmp_kernel(p.shape, p.one) : mmp_kernel(p.shape, p.one));
-    } else if (make_streamed(m, algo, T, sa, p.lds, p.threads)) {
-        a = &sa.a;
-        args[0] = &sa;
-        fn = algo == BI_ALGO_VMP ? vmp_streamed() : mmp_streamed();
-    } else {
-        return kNoPlan;
-    }
+    Choice c;
+    if (!choose(m, algo, b, T, c)) return kNoPlan;
+    Args *a = c.a;
     a->base = m->dev;
     a->iters = iters;
     a->obs = obs;
@@ -659,10 +694,11 @@ int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *ob
     a->prior = prior;
     a->tau = tau;
     a->q = q;
-    hipError_t e = func_max_lds(fn, (int)kLds);
+    void *args[1] = {c.args};
+    hipError_t e = func_max_lds(c.fn, (int)kLds);
     if (e == hipSuccess) {
-        ProfScope ps(fpi ? "agent_filter_tile" : "agent_window_tile", stream);
-        e = hipLaunchKernel(fn, dim3(b), dim3(p.threads), args, p.lds, stream);
+        ProfScope ps(c.name, stream);
+        e = hipLaunchKernel(c.fn, dim3(b), dim3(c.p.threads), args, c.p.lds, stream);
     }
     if (e != hipSuccess) return fail(BI_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return BI_OK;

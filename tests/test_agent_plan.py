@@ -1,0 +1,77 @@
+"""The plans of agent-resident calls (host only): the models of
+test_gpu_resident.py and test_gpu_agent_tile.py reach the kernels and forms
+that those files say they test."""
+import numpy as np
+import pytest
+
+from paper_2607_17855_amd import synth
+from agent_plan import plan_of
+import test_gpu_agent_tile as tile
+import test_gpu_resident as res
+
+ALGOS = ("fpi", "vmp", "mmp")
+
+
+@pytest.mark.parametrize("form", range(len(res.FORMS)))
+def test_resident_forms(form):
+    n, U, deps, lists, T, fpi, vmp, *mmp = res.FORMS[form]
+    w, _ = res.form_workload(form)
+    kind = "coupled" if lists else "resident"
+    for algo, text in zip(ALGOS, (fpi, vmp, mmp[0] if mmp else vmp)):
+        p = plan_of(w.model, w.b, w.T, algo)
+        assert p["kernel"] == res.kernel_of(kind, algo), p
+        assert (p["tile"] if algo == "fpi" else f"{p['tile']} {p['tables']} {p['passes']}") == text, p
+
+
+def test_every_kernel_has_a_form():
+    tiles = {"1x1", "2x1", "4x1", "8x1", "2x2", "4x2", "8x2", "4x4", "6x4", "12x2", "8x4", "12x4", "12x5", "8x8"}
+    passes = {"one", "several"}
+    for algo in (0, 1):
+        plain = [(f[6:] * 2)[algo].split() for f in res.FORMS if not f[3]]
+        coupled = [(f[6:] * 2)[algo].split() for f in res.FORMS if f[3]]
+        assert {(t, p) for t, _, p in plain} == {(t, p) for t in tiles for p in passes}
+        assert {(b, p) for _, b, p in plain} == {(b, p) for b in ("twice", "once", "packed") for p in passes}
+        assert {tuple(c) for c in coupled} == (
+            {(t, "lds", p) for t in ("1x1", "2x2", "4x2", "4x4", "6x4", "12x4", "12x5") for p in passes}
+            | {(t, "packed", p) for t in ("2x2", "4x2", "12x4") for p in passes})
+    assert {f[5] for f in res.FORMS if not f[3]} == tiles
+
+
+@pytest.mark.parametrize("algo", ALGOS)
+def test_resident_cases(algo):
+    for kind, names, make in (("resident", res.CASES, res._workload), ("streamed", res.STREAMED, res._workload),
+                              ("coupled", res.COUPLED, res._coupled)):
+        for name in names:
+            w, _ = make(name)
+            p = plan_of(w.model, w.b, w.T, algo)
+            assert p["kernel"] == res.kernel_of(kind, algo, w.T), (name, p)
+    w, _ = res._coupled("long_lists")
+    assert plan_of(w.model, w.b, w.T, "fpi")["kernel"] == "agent_filter_resident"
+
+
+@pytest.mark.parametrize("algo", ("vmp", "mmp"))
+def test_streamed_cases(algo):
+    """The three places of the tables; windows at once and in chunks."""
+    plans = []
+    for name in res.STREAMED:
+        w, _ = res._workload(name)
+        plans.append((w.T, plan_of(w.model, w.b, w.T, algo)))
+    assert {p["tables"] for _, p in plans} == {"twice", "once", "packed"}
+    assert {int(p["chunk"]) < T for T, p in plans} == {True, False}
+    assert {int(p["steps"]) < T for T, p in plans} == {True, False}
+
+
+def _model(n, U, K, deps):
+    return synth.make_model(np.random.Generator(np.random.PCG64(1)), n, U, K, deps, 1, 1.0, 1.0)
+
+
+def test_tile_cases():
+    for (n, U, K, deps, b, T, _), kernel in zip(tile.CASES, tile.KERNEL):
+        for algo in ("vmp", "mmp"):
+            assert plan_of(_model(n, U, K, deps), b, T, algo)["kernel"] == kernel
+    for (n, K, deps, b, T), (fpi, window) in zip(tile.FPI_CASES, tile.FPI_KERNEL):
+        for algo in ALGOS:
+            assert plan_of(_model(n, [2] * len(n), K, deps), b, T, algo)["kernel"] == (fpi if algo == "fpi" else window)
+    for n, U, K, deps, b, T, *form in tile.FORMS.values():
+        for algo in ALGOS:
+            assert plan_of(_model(n, U, K, deps), b, T, algo).get("src", "") == form[algo != "fpi"]

@@ -36,10 +36,16 @@ def _agents(seed, n, K, deps, b, T, algos):
 CASES = [
     # (workload maker, packing flags, algorithms, kernel family)
     (lambda: synth.two_factor_agents(b=32), bi.BI_DENSE_A, ("fpi", "vmp", "mmp"), "agent"),
-    # windows read from global memory (tile form), and FPI steps in the tile form
+    # windows and FPI steps with the largest register tiles
     (lambda: _agents(1204, [20, 6, 7], [5, 3, 4], [[0, 1, 2], [1], [0, 2]], 6, 12, ("vmp", "mmp")),
      bi.BI_DENSE_A, ("vmp", "mmp"), "agent"),
     (lambda: _agents(1205, [30, 25, 28], [3, 4], [[0, 1, 2], [2]], 3, 4, ("fpi",)), bi.BI_DENSE_A, ("fpi",), "agent"),
+    # beyond the register-resident plans: windows read from global memory (tile
+    # form; nine factors), FPI steps in the tile form, streamed windows
+    (lambda: _agents(1206, [20, 6, 7] + [2] * 6, [5, 3, 4], [[0, 1, 2], [1], [0, 2]], 6, 12, ("vmp", "mmp")),
+     bi.BI_DENSE_A, ("vmp", "mmp"), "agent"),
+    (lambda: _agents(1207, [40, 28, 31], [3, 4], [[0, 1, 2], [2]], 3, 4, ("fpi", "vmp", "mmp")), bi.BI_DENSE_A,
+     ("fpi", "vmp", "mmp"), "agent"),
     (lambda: _shared(1200, [9, 7, 5], [2, 1, 3], [3, 2, 4], [[0, 1, 2], [1], [0, 2]], 24, 5),
      bi.BI_DENSE_A | bi.BI_FAST_F32, ("vmp", "mmp"), "stream"),
     (lambda: _shared(1201, [4, 32, 6, 32], [2, 1, 2, 1], [3], [[0, 1, 2, 3]], 30, 4),

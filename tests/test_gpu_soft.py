@@ -77,8 +77,8 @@ def test_soft_one_hot_equals_integer_observations(seed):
         pm.close()
 
 
-# larger slices: the window no longer fits in LDS (per-step staging, or the
-# slices read from the workspace), rank-3 and rank-4 modalities, many steps
+# larger slices (tensors streamed from the workspace, or held in large register
+# tiles), rank-3 and rank-4 modalities, many steps
 LARGE = [
     # (n, U, K, deps, b, T, per_agent)
     ([24, 20, 16], [2, 1, 3], [6, 3], [[0, 1, 2], [1, 2]], 6, 7, True),
