@@ -1276,7 +1276,7 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     // states, and windows of more than eight modalities that exceed registers.
     // (After the check above: windows too long for those kernels stay refused,
     // whichever kernel would run them.)
-    rc = launch_resident(m, algo, b, T, obs, ll, act, prior, tau, iters, q, stream);
+    rc = launch_resident(m, algo, b, T, a.stage == kStageWindow, obs, ll, act, prior, tau, iters, q, stream);
     if (rc != kNoPlan) return rc;
     a.base = m->dev;
     a.mods = reinterpret_cast<const ModDesc *>(m->dev);
@@ -1344,7 +1344,7 @@ extern "C" int bi_test_agent_plan(const bi_model *model, int32_t b, int32_t T, i
         size_t lds = 0;
         const int rc = plan_agent(model, algo, T, a, lds);
         if (rc != BI_OK) return rc;
-        if (describe_resident(model, algo, b, T, buf, cap)) return BI_OK;
+        if (describe_resident(model, algo, b, T, a.stage == kStageWindow, buf, cap)) return BI_OK;
         static const char *srcs[] = {"lds", "global", "tile", "lds_short"};
         std::snprintf(buf, cap, "%s src=%s chunk=%d tables=%s lds=%zu", class_name(algo, a),
                       algo == BI_ALGO_FPI ? srcs[a.tile ? kSrcTile : a.stage == kStageNone ? kSrcGlobal : kSrcLds]

@@ -628,6 +628,20 @@ bool make_streamed(const bi_model *m, int algo, int T, StreamedArgs &best, size_
     return cost >= 0.0;
 }
 
+// Whether a window that the kernels of agent.hip would hold in LDS (staged)
+// runs better there than streamed.  Their workgroups of 4 waves share a compute
+// unit by fours and more; the streamed kernel's 209 registers leave a unit 8
+// waves, so where its workgroups do not all fit at once they take turns.  On
+// 596 staged windows of 5 to 8 maximal lists (2 to 9 states a factor, 1 to 20
+// steps, 1 to 2048 agents, 16 sweeps) the streamed kernel was 1.00 to 5.0 times
+// as fast on all 526 that fit, and 0.42 to 1.84 times (0.93 in the geometric
+// mean) on the other 70: 1438 agents, 5 steps, VMP 226 us staged, 542 us streamed.
+bool staged_is_better(int b, int threads, bool staged)
+{
+    constexpr int kWavesFit = 8;
+    return staged && div_up(b, kCus) * (threads / 64) > kWavesFit;
+}
+
 // The kernel and arguments of a call.
 struct Choice {
     Plan p;           // (streamed: lds and threads of it)
@@ -638,7 +652,7 @@ struct Choice {
     void *args;
 };
 
-bool choose(const bi_model *m, int algo, int b, int T, Choice &c)
+bool choose(const bi_model *m, int algo, int b, int T, bool staged, Choice &c)
 {
     const bool fpi = algo == BI_ALGO_FPI, vmp = algo == BI_ALGO_VMP;
     Plan &p = c.p;
@@ -651,7 +665,7 @@ bool choose(const bi_model *m, int algo, int b, int T, Choice &c)
         c.name = fpi ? "agent_filter_resident" : p.coupled ? "agent_window_coupled" : "agent_window_resident";
         return true;
     }
-    if (make_streamed(m, algo, T, c.sa, p.lds, p.threads)) {
+    if (make_streamed(m, algo, T, c.sa, p.lds, p.threads) && !staged_is_better(b, p.threads, staged)) {
         c.a = &c.sa.a;
         c.args = &c.sa;
         c.fn = vmp ? vmp_streamed() : mmp_streamed();
@@ -663,10 +677,10 @@ bool choose(const bi_model *m, int algo, int b, int T, Choice &c)
 
 }  // namespace
 
-bool describe_resident(const bi_model *m, int algo, int b, int T, char *buf, size_t cap)
+bool describe_resident(const bi_model *m, int algo, int b, int T, bool staged, char *buf, size_t cap)
 {
     Choice c;
-    if (!choose(m, algo, b, T, c)) return false;
+    if (!choose(m, algo, b, T, staged, c)) return false;
     static const char *tabs[] = {"packed", "once", "twice"};
     const Plan &p = c.p;
     if (c.a == &c.sa.a)
@@ -680,11 +694,11 @@ bool describe_resident(const bi_model *m, int algo, int b, int T, char *buf, siz
     return true;
 }
 
-int launch_resident(const bi_model *m, int algo, int b, int T, const int32_t *obs, const double *ll,
+int launch_resident(const bi_model *m, int algo, int b, int T, bool staged, const int32_t *obs, const double *ll,
                     const int32_t *act, const float *prior, double tau, int iters, float *q, hipStream_t stream)
 {
     Choice c;
-    if (!choose(m, algo, b, T, c)) return kNoPlan;
+    if (!choose(m, algo, b, T, staged, c)) return kNoPlan;
     Args *a = c.a;
     a->base = m->dev;
     a->iters = iters;

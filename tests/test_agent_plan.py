@@ -61,6 +61,24 @@ def test_streamed_cases(algo):
     assert {int(p["steps"]) < T for T, p in plans} == {True, False}
 
 
+@pytest.mark.parametrize("algo", ("vmp", "mmp"))
+def test_small_windows_of_many_lists(algo):
+    """More than four maximal lists in a window that fits LDS: streamed while
+    all workgroups (8 waves to a compute unit) run at once, else staged; a
+    window that does not fit LDS is streamed for any number of agents."""
+    small = _model([3, 4, 2, 3, 4, 2], [2, 1, 2, 1, 1, 1], [4] * 5, [[0, 1], [1, 2], [2, 3], [3, 4], [4, 5]])
+    waves = int(plan_of(small, 1, 9, algo)["threads"]) // 64
+    assert 2 <= waves <= 4
+    fit = 8 // waves * 256
+    for b in (1, 256, fit):
+        assert plan_of(small, b, 9, algo)["kernel"] == "agent_window_streamed"
+    for b in (fit + 1, 2048, 100000):
+        assert plan_of(small, b, 9, algo)["kernel"] == "agent_window"
+    large = _model([20, 18, 16, 3, 4, 2], [2, 1, 2, 1, 1, 1], [4] * 5, [[0, 1], [1, 2], [2, 3], [3, 4], [4, 5]])
+    for b in (1, 2048):
+        assert plan_of(large, b, 20, algo)["kernel"] == "agent_window_streamed"
+
+
 def _model(n, U, K, deps):
     return synth.make_model(np.random.Generator(np.random.PCG64(1)), n, U, K, deps, 1, 1.0, 1.0)
 
