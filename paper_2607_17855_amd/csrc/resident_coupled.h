@@ -403,6 +403,34 @@ __global__ __launch_bounds__(max_threads(RB, CB, true)) void coupled_kernel(Coup
 #define BI_RES_COUPLED(X) X(0, 1, 1) X(4, 2, 2) X(5, 4, 2) X(7, 4, 4) X(8, 6, 4) X(11, 12, 4) X(12, 12, 5)
 #define BI_RES_COUPLED_PACKED(X) X(4, 2, 2) X(5, 4, 2) X(11, 12, 4)
 
+template <int ALGO, int I, int R, int C, bool LT>
+const void *coupled_passes(bool one)
+{
+    static_assert(kShapes[I].rb == R && kShapes[I].cb == C, "shape");
+    return one ? (const void *)coupled_kernel<ALGO, R, C, true, LT> : (const void *)coupled_kernel<ALGO, R, C, false, LT>;
+}
+
+template <int ALGO>
+const void *coupled_of(int shape, bool one, bool lds_tab)
+{
+    if (lds_tab) {
+        switch (shape) {
+#define BI_X(i, r, c) \
+    case i: return coupled_passes<ALGO, i, r, c, true>(one);
+            BI_RES_COUPLED(BI_X)
+#undef BI_X
+        }
+    } else {
+        switch (shape) {
+#define BI_X(i, r, c) \
+    case i: return coupled_passes<ALGO, i, r, c, false>(one);
+            BI_RES_COUPLED_PACKED(BI_X)
+#undef BI_X
+        }
+    }
+    return nullptr;
+}
+
 // nullptr: not built for this shape.
 const void *vmp_coupled(int shape, bool one, bool lds_tab);
 const void *mmp_coupled(int shape, bool one, bool lds_tab);

@@ -5,33 +5,7 @@
 namespace bi {
 namespace res {
 
-template <int I, int R, int C, bool LT>
-static const void *pick(bool one)
-{
-    static_assert(kShapes[I].rb == R && kShapes[I].cb == C, "shape");
-    return one ? (const void *)coupled_kernel<BI_ALGO_MMP, R, C, true, LT>
-               : (const void *)coupled_kernel<BI_ALGO_MMP, R, C, false, LT>;
-}
-
-const void *mmp_coupled(int shape, bool one, bool lds_tab)
-{
-    if (lds_tab) {
-        switch (shape) {
-#define BI_X(i, r, c) \
-    case i: return pick<i, r, c, true>(one);
-            BI_RES_COUPLED(BI_X)
-#undef BI_X
-        }
-    } else {
-        switch (shape) {
-#define BI_X(i, r, c) \
-    case i: return pick<i, r, c, false>(one);
-            BI_RES_COUPLED_PACKED(BI_X)
-#undef BI_X
-        }
-    }
-    return nullptr;
-}
+const void *mmp_coupled(int shape, bool one, bool lds_tab) { return coupled_of<BI_ALGO_MMP>(shape, one, lds_tab); }
 
 }  // namespace res
 }  // namespace bi

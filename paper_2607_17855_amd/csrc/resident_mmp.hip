@@ -1,19 +1,10 @@
-// MMP instantiations of the register-resident window kernel (a file of its
-// own, so the shapes of the three algorithms compile side by side).
-#include "resident_kernel.h"
+// MMP instantiations of the register-resident window kernel.
+#include "resident_window.h"
 
 namespace bi {
 namespace res {
 
-const void *mmp_kernel(int shape, bool one)
-{
-    static const void *const tab[][2] = {
-#define BI_X(r, c) {(const void *)window_kernel<BI_ALGO_MMP, r, c, false>, (const void *)window_kernel<BI_ALGO_MMP, r, c, true>},
-        BI_RES_SHAPES(BI_X)
-#undef BI_X
-    };
-    return tab[shape][one];
-}
+const void *mmp_kernel(int shape, bool one) { return window_of<BI_ALGO_MMP>(shape, one); }
 
 }  // namespace res
 }  // namespace bi

@@ -1,19 +1,10 @@
-// VMP instantiations of the register-resident window kernel (a file of its
-// own, so the shapes of the three algorithms compile side by side).
-#include "resident_kernel.h"
+// VMP instantiations of the register-resident window kernel.
+#include "resident_window.h"
 
 namespace bi {
 namespace res {
 
-const void *vmp_kernel(int shape, bool one)
-{
-    static const void *const tab[][2] = {
-#define BI_X(r, c) {(const void *)window_kernel<BI_ALGO_VMP, r, c, false>, (const void *)window_kernel<BI_ALGO_VMP, r, c, true>},
-        BI_RES_SHAPES(BI_X)
-#undef BI_X
-    };
-    return tab[shape][one];
-}
+const void *vmp_kernel(int shape, bool one) { return window_of<BI_ALGO_VMP>(shape, one); }
 
 }  // namespace res
 }  // namespace bi
