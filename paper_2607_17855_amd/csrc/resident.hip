@@ -308,6 +308,7 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
     const bool coupled = !m->trivial_b && algo != BI_ALGO_FPI && T > 1;
     out.coupled = coupled;
     const bool fpi = algo == BI_ALGO_FPI;
+    if (!fpi && !coupled && !vmp_kernel(shape, false)) return false;
     const int contexts = fpi ? 1 : T, maxthreads = max_threads(rb, cb, fpi || coupled);
     int role[kMaxG][kRoles];
     int room[kMaxF];   // marginals of a factor that a tile may read (its states and padding)

@@ -9,7 +9,7 @@ const void *fpi_kernel(int shape)
 {
     static const void *const tab[] = {
 #define BI_X(r, c) (const void *)filter_kernel<r, c, true>,
-        BI_RES_SHAPES(BI_X)
+        BI_RES_SHAPES(BI_X, BI_X)
 #undef BI_X
     };
     return tab[shape];

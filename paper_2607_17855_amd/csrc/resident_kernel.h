@@ -872,16 +872,25 @@ __global__ __launch_bounds__(max_threads(RB, CB, true)) void filter_kernel(Args 
     }
 }
 
-// Tile shapes (rows x columns per lane) the kernels are built for.
-#define BI_RES_SHAPES(X) \
-    X(1, 1) X(2, 1) X(4, 1) X(8, 1) X(2, 2) X(4, 2) X(8, 2) X(4, 4) X(6, 4) X(12, 2) X(8, 4) X(12, 4) X(12, 5) X(8, 8)
+// Tile shapes (rows x columns per lane) the kernels are built for; F: the
+// filter only.  What a shape gives: the time of the calls that plan it (up to
+// 28 each, drawn from 1 to 8 factors of 2 to 64 states, 1 to 200 steps, 1 to
+// 2048 agents) when they have to do without it, in the geometric mean.
+// Windows: 1 x 1 to 4 x 2 1.01 to 1.02, 8 x 1 1.04 (at most 1.9), 8 x 2 1.04,
+// 4 x 4 1.04, 6 x 4 1.01 (at most 2.9), 8 x 4 1.08, 12 x 4 1.11, 12 x 5 1.75
+// and 8 x 8 1.85 (both up to 12, where no other plan fits); 12 x 2 0.94 (0.80
+// to 1.03: with 1024 threads it spills), so windows are not built for it.
+// Filter: 0.97 to 1.06 up to 8 x 2 and 6 x 4, 12 x 2 1.01 (at most 1.9), 8 x 4
+// 1.11, 12 x 4 1.15, 8 x 8 1.10 and 12 x 5 1.47 (both up to 13).
+#define BI_RES_SHAPES(X, F) \
+    X(1, 1) X(2, 1) X(4, 1) X(8, 1) X(2, 2) X(4, 2) X(8, 2) X(4, 4) X(6, 4) F(12, 2) X(8, 4) X(12, 4) X(12, 5) X(8, 8)
 
 struct Shape {
     int rb, cb;
 };
 constexpr Shape kShapes[] = {
 #define BI_X(r, c) {r, c},
-    BI_RES_SHAPES(BI_X)
+    BI_RES_SHAPES(BI_X, BI_X)
 #undef BI_X
 };
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
@@ -889,6 +898,7 @@ constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 // Kernels by shape (the files named above).
 const void *fpi_kernel(int shape);
 const void *fpi_coupled(int shape);   // general B-dependency lists
+// nullptr: not built for this shape
 const void *vmp_kernel(int shape, bool one);
 const void *mmp_kernel(int shape, bool one);
 

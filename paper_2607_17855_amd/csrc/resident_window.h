@@ -13,7 +13,9 @@ const void *window_of(int shape, bool one)
 {
     static const void *const tab[][2] = {
 #define BI_X(r, c) {(const void *)window_kernel<ALGO, r, c, false>, (const void *)window_kernel<ALGO, r, c, true>},
-        BI_RES_SHAPES(BI_X)
+#define BI_F(r, c) {nullptr, nullptr},
+        BI_RES_SHAPES(BI_X, BI_F)
+#undef BI_F
 #undef BI_X
     };
     return tab[shape][one];

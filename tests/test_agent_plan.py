@@ -29,7 +29,7 @@ def test_every_kernel_has_a_form():
     for algo in (0, 1):
         plain = [(f[6:] * 2)[algo].split() for f in res.FORMS if not f[3]]
         coupled = [(f[6:] * 2)[algo].split() for f in res.FORMS if f[3]]
-        assert {(t, p) for t, _, p in plain} == {(t, p) for t in tiles for p in passes}
+        assert {(t, p) for t, _, p in plain} == {(t, p) for t in tiles - {"12x2"} for p in passes}   # (the filter's alone)
         assert {(b, p) for _, b, p in plain} == {(b, p) for b in ("twice", "once", "packed") for p in passes}
         assert {tuple(c) for c in coupled} == (
             {(t, "lds", p) for t in ("1x1", "2x2", "4x2", "4x4", "6x4", "12x4", "12x5") for p in passes}

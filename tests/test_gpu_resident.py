@@ -86,13 +86,12 @@ FORMS = [
     ([5, 5, 5, 4], [1, 4, 2, 4], [[0, 1, 2, 3], [1]], None, 2, "6x4", "6x4 twice one"),
     ([2, 3, 3, 13], [2, 1, 2, 3], [[0, 2], [0, 1, 2, 3]], None, 2, "8x1", "8x1 twice one"),
     ([3, 13, 7, 5], [4, 1, 1, 4], [[0, 2], [0, 1, 2, 3]], None, 2, "8x4", "8x4 twice one"),
-    ([4, 4, 5, 17], [2, 2, 5, 1], [[0, 1, 2, 3]], None, 2, "12x2", "12x2 twice one"),
+    ([4, 4, 5, 17], [2, 2, 5, 1], [[0, 1, 2, 3]], None, 2, "12x2", "8x2 twice one"),
     ([3, 13, 4, 13], [5, 1, 3, 1], [[2]], None, 20, "1x1", "1x1 twice several"),
     ([3, 25, 5], [3, 1, 3], [[0, 2]], None, 20, "1x1", "8x1 twice several"),
     ([12, 17, 2, 2], [1, 2, 4, 1], [[0, 2]], None, 20, "2x1", "4x1 twice several"),
     ([4, 26, 4], [3, 1, 2], [[0, 2]], None, 20, "1x1", "4x4 twice several"),
     ([12, 2, 12, 7], [4, 1, 3, 3], [[1, 3]], None, 20, "1x1", "2x1 twice several"),
-    ([3, 30], [3, 1], [[0, 1], [0]], None, 20, "4x1", "12x2 twice several"),
     ([5, 20, 5, 7], [2, 2, 3, 1], [[0, 1, 2, 3]], None, 2, "12x4", "12x4 twice one"),
     ([2, 9, 9, 20], [2, 5, 3, 1], [[2, 3], [0, 1, 2, 3]], None, 2, "12x5", "12x5 twice one"),
     ([5, 17, 2, 9], [1, 3, 3, 2], [[1, 2], [2, 3]], None, 32, "2x1", "4x2 twice several", "6x4 twice several"),
@@ -103,7 +102,7 @@ FORMS = [
     ([33, 5], [1, 1], [[0, 1]], None, 32, "4x1", "12x5 once several", "12x5 twice several"),
     ([20, 9, 7], [2, 1, 5], [[0, 1], [2]], None, 32, "2x1", "8x4 once several", "8x4 twice several"),
     ([7, 4, 33], [1, 4, 1], [[1, 2]], None, 32, "4x1", "12x4 once several", "12x4 twice several"),
-    ([9, 5, 5, 3], [3, 2, 5, 2], [[0, 1, 2, 3]], None, 20, "4x2", "12x2 packed one"),
+    ([5, 17, 5, 4], [1, 5, 4, 2], [[0, 3], [0, 1, 2]], None, 32, "4x1", "6x4 packed one"),
     ([13, 5, 9, 9], [2, 5, 2, 4], [[0, 1, 2]], None, 20, "4x2", "8x8 twice several"),
     ([7, 5, 13], [2, 1, 5], [[1], [0, 1, 2]], None, 32, "4x2", "6x4 once one"),
     ([2, 2], [1, 1], [[1], [1]], [[0], [0, 1]], 2, "1x1", "1x1 lds one"),
