@@ -68,9 +68,12 @@ LAYOUTS = ("dense", "sparse")
 ALGOS = ("vmp", "mmp")
 
 
-def source_sha(fname: str) -> str:
-    with open(os.path.join(CSRC, fname), "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()[:16]
+def source_sha(*fnames: str) -> str:
+    h = hashlib.sha256()
+    for fname in fnames:
+        with open(os.path.join(CSRC, fname), "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()[:16]
 
 
 import numpy as np   # noqa: E402  (host-side arithmetic of the work counts)
@@ -146,16 +149,39 @@ def sparse16_lik_work(model, obs, soft=None):
     return flops, nbytes, 2 * nbytes
 
 
-def agent_work(model, T, algo):
+# kernels of the agent-resident path by profile class: name, sources, and
+# whether they contract one merged tensor per maximal dependency list, loaded
+# once per call (the others: every modality's slice, read in every sweep)
+AGENT_KERNELS = {
+    "agent_window_resident": ("window_kernel", ("resident_kernel.h", "resident.hip"), True),
+    "agent_filter_resident": ("filter_kernel", ("resident_kernel.h", "resident.hip"), True),
+    "agent_window_coupled": ("coupled_kernel", ("resident_coupled.h", "resident_kernel.h", "resident.hip"), True),
+    "agent_window_streamed": ("streamed_kernel", ("resident_streamed.h", "resident_kernel.h", "resident.hip"), False),
+    "agent_window": ("agent_window_kernel", ("agent.hip",), False),
+    "agent_window_tile": ("agent_window_kernel", ("agent.hip",), False),
+    "agent_filter": ("agent_filter_kernel", ("agent.hip",), False),
+    "agent_filter_tile": ("agent_filter_kernel", ("agent.hip",), False),
+}
+
+
+def merged_sizes(model):
+    """Entries of the merged tensors: one per maximal dependency list."""
+    lists = [set(d) for d in model.deps]
+    top = [d for i, d in enumerate(lists) if not any(d < e or (d == e and j < i) for j, e in enumerate(lists))]
+    return [int(np.prod([model.n[f] for f in d])) for d in top]
+
+
+def agent_work(model, T, algo, merged=False):
     """Algorithmic flops and bytes of one belief update on the agent-resident
-    path: the two contractions of every observed slice (one FMA per entry
-    each), the transition messages (per state of f: the forward contraction
-    over the states of f's B-dependency list, and for every factor j whose
-    list holds f the backward one over s_{t+1}^j and j's other listed
-    factors; two n x n products per factor for trivial lists; FPI: the
-    forward one only, once per time step, counted per update), and one read
-    of the observed fp64 slices."""
-    lik = sum(4 * P for P in slice_sizes(model))
+    path: the two contractions of every observed slice, or with `merged` of
+    every merged tensor (one FMA per entry each), the transition messages (per
+    state of f: the forward contraction over the states of f's B-dependency
+    list, and for every factor j whose list holds f the backward one over
+    s_{t+1}^j and j's other listed factors; two n x n products per factor for
+    trivial lists; FPI: the forward one only, once per time step, counted per
+    update), and one read of the observed fp64 slices (with `merged` once per
+    call, not per update)."""
+    lik = sum(4 * P for P in (merged_sizes(model) if merged else slice_sizes(model)))
     bstates = [int(np.prod([model.n[g] for g in model.bdep(f)])) for f in range(model.F)]
     trans = 0
     for f, n in enumerate(model.n):
@@ -755,7 +781,8 @@ def bench_agent(args, bi, synth, torch, dev):
     cls = next(k for k in prof if k.startswith("agent_"))   # (a call runs one of them)
     launches, total_ms = prof[cls]
     avg_ms = total_ms / max(launches, 1)
-    fl, nb = agent_work(w.model, w.T, algo)
+    kname, sources, merged = AGENT_KERNELS[cls]
+    fl, nb = agent_work(w.model, w.T, algo, merged)
     t_launch = 1 if rolling else w.T   # steps per launch
     flops = fl * w.b * t_launch * w.iters
     achieved = flops / (avg_ms / 1e3) / 1e12
@@ -774,21 +801,21 @@ def bench_agent(args, bi, synth, torch, dev):
         "wall_s_timed": wall,
     }
     # Both rooflines of the agent kernel: the fp64 arithmetic, and the bytes
-    # of one read of the observed fp64 slices per belief update (its counted
-    # traffic from profiles/traffic_agent.json while the kernel source is
-    # unchanged).  The counters show the kernel waiting on memory, not on
-    # arithmetic; the headline roofline is the one it is closer to.
-    alg_bytes = nb * w.b * t_launch * w.iters
+    # of one read of the observed fp64 slices per belief update, or per launch
+    # where they are merged into registers (its counted traffic from
+    # profiles/traffic_agent.json while the kernel sources are unchanged).  The
+    # headline roofline is the one the kernel is closer to.
+    alg_bytes = nb * w.b * t_launch * (1 if merged else w.iters)
     tr = load_agent_traffic().get(args.workload)
-    hbm = tr["hbm_bytes_per_launch"] if tr and tr.get("kernel_source_sha") == source_sha("agent.hip") else None
+    hbm = tr["hbm_bytes_per_launch"] if tr and tr.get("kernel_source_sha") == source_sha(*sources) else None
     gbps = alg_bytes / (avg_ms / 1e3) / 1e9
     out["roofline_all"] = {
         "hbm": {"bound": "hbm", "achieved": gbps, "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": gbps / PEAK_HBM_GBPS,
-                "traffic": hbm, "kernel": cls + "_kernel", "avg_launch_ms": avg_ms, "launches": launches,
+                "traffic": hbm, "kernel": kname, "avg_launch_ms": avg_ms, "launches": launches,
                 "algorithmic_bytes_per_launch": alg_bytes,
                 "measured_hbm_GBps": None if hbm is None else hbm / (avg_ms / 1e3) / 1e9},
         "alu": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP64_VALU_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / PEAK_FP64_VALU_TFLOPS, "traffic": hbm, "kernel": cls + "_kernel",
+                "frac": achieved / PEAK_FP64_VALU_TFLOPS, "traffic": hbm, "kernel": kname,
                 "avg_launch_ms": avg_ms, "launches": launches, "algorithmic_flops_per_launch": flops}}
     out["roofline"] = max(out["roofline_all"].values(), key=lambda r: r["frac"])
     if soft_np is not None:

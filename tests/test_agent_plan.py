@@ -93,3 +93,16 @@ def test_tile_cases():
     for n, U, K, deps, b, T, *form in tile.FORMS.values():
         for algo in ALGOS:
             assert plan_of(_model(n, U, K, deps), b, T, algo).get("src", "") == form[algo != "fpi"]
+
+
+def test_bench_knows_every_kernel():
+    """The benchmark's record names the kernel of each profile class and its
+    sources, and counts merged tensors once per maximal list."""
+    import bench
+    kernels = {"agent_window", "agent_window_tile", "agent_filter", "agent_filter_tile", "agent_filter_resident",
+               "agent_window_resident", "agent_window_coupled", "agent_window_streamed"}
+    assert set(bench.AGENT_KERNELS) == kernels
+    for name, sources, _ in bench.AGENT_KERNELS.values():
+        assert any(f" {name}(" in open(f"{bench.CSRC}/{s}").read() for s in sources)
+    m = _model([2, 3, 5, 7], [1] * 4, [2] * 6, [[0], [0, 1], [0, 1], [1, 2], [3], [2]])
+    assert sorted(bench.merged_sizes(m)) == [6, 7, 15]
