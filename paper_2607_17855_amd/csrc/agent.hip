@@ -1,4 +1,5 @@
-// Agent-resident kernels: one workgroup (256 threads, 4 waves) per agent runs
+// Agent-resident kernels for the calls that the register-resident ones do not
+// take (launch_agent lists them): one workgroup (256 threads, 4 waves) per agent runs
 // every iteration of FPI, VMP or MMP without leaving the kernel.  Marginals,
 // likelihood messages and the Z/V scratch of the two-sided slice view live in
 // LDS; the emission slices, B and D are read from the packed buffer (L2 /
@@ -1264,18 +1265,28 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     int rc = plan_agent(m, algo, T, a, lds);
     if (rc != BI_OK) return rc;
     // The register-resident kernels take every call that they have a plan for,
-    // the streamed one the other windows with trivial B-dependency lists: on
-    // 904 calls of sweep models (FPI, VMP and MMP, 256 agents sharing a model,
-    // 16 sweeps) they were 1.02 to 9 times faster than the kernels below, the
-    // resident ones in sum 260 -> 71 ms (FPI), 94 -> 52 ms (VMP), 97 -> 52 ms
-    // (MMP), the streamed one 100 -> 83 ms (VMP and MMP each; by time mostly
-    // one tensor that all agents read from beyond L2, 1.05 times, otherwise
-    // 1.1 to 4.3 times).  What is left for the kernels below: lists of more
-    // than four factors, B-dependency lists of more than two (VMP, MMP) or
-    // windows with such lists that exceed a workgroup, factors of more than 64
-    // states, and windows of more than eight modalities that exceed registers.
-    // (After the check above: windows too long for those kernels stay refused,
-    // whichever kernel would run them.)
+    // the streamed one the other windows with trivial B-dependency lists.  On
+    // the 1540 sweep models (256 agents sharing a model, 16 sweeps) against the
+    // kernels below: 1519 FPI calls in sum 1283 -> 293 ms, 1395 VMP windows
+    // 273 -> 77 ms and as many MMP ones 288 -> 72 ms (1.1 to 36 times as fast,
+    // every call), 145 streamed windows each 430 -> 261 and 422 -> 257 ms (1.02 to
+    // 5.9 times, but for one at 0.91: 15 x 32 x 24 x 6 states, 8 steps, VMP).
+    // What is left for the kernels below:
+    //  - likelihood lists of more than four factors, factors of more than 64
+    //    states, more than 8 factors or 16 modalities, transition tables of more
+    //    than 160 K elements (kMaxF and the other limits of plan_base);
+    //  - FPI: more than four maximal lists, or a step whose merged tensors
+    //    exceed a workgroup's registers (32768 values on 8 x 8 tiles);
+    //  - VMP and MMP with B-dependency lists: a list of more than two factors,
+    //    more than four maximal likelihood lists, or a window that exceeds a
+    //    workgroup's registers or LDS;
+    //  - other windows that exceed a workgroup's registers or LDS, or have more
+    //    than four maximal lists, and cannot be streamed (more than eight
+    //    modalities, more than 512 lanes for one step, or too many steps: one
+    //    step's lines beside the window's marginals must fit LDS, which 100 steps
+    //    of 20 + 6 + 7 states do not), or that stay staged (staged_is_better).
+    // (After the check above: windows too long for the kernels below stay
+    // refused, whichever kernel would run them.)
     rc = launch_resident(m, algo, b, T, a.stage == kStageWindow, obs, ll, act, prior, tau, iters, q, stream);
     if (rc != kNoPlan) return rc;
     a.base = m->dev;
