@@ -1269,8 +1269,9 @@ int launch_agent(const bi_model *m, int algo, int b, int T, const int32_t *obs, 
     // the 1540 sweep models (256 agents sharing a model, 16 sweeps) against the
     // kernels below: 1519 FPI calls in sum 1283 -> 293 ms, 1395 VMP windows
     // 273 -> 77 ms and as many MMP ones 288 -> 72 ms (1.1 to 36 times as fast,
-    // every call), 145 streamed windows each 430 -> 261 and 422 -> 257 ms (1.02 to
-    // 5.9 times, but for one at 0.91: 15 x 32 x 24 x 6 states, 8 steps, VMP).
+    // every call), 145 streamed windows each 428 -> 260 and 420 -> 255 ms (1.02 to
+    // 6.0 times).  Of 234 larger streamed windows three are slower (0.92 to 0.99;
+    // 311 to 438 agents, whose second round leaves compute units idle).
     // What is left for the kernels below:
     //  - likelihood lists of more than four factors, factors of more than 64
     //    states, more than 8 factors or 16 modalities, transition tables of more

@@ -513,6 +513,14 @@ bool plan_streamed(const bi_model *m, int algo, int T, const Args &base, int blo
         s.na = div_up(s.n[kRow], kBlk);
         s.nb = div_up(s.n[kCol], kBlk);
         s.per = std::min(s.n[kP], std::max(1, blocks / s.n[kO2]));
+        // The walked states whose values lie closer together go innermost: a
+        // cache line that a lane's block takes in part is then finished in the
+        // next steps of the walk, while it is still in the compute unit's cache
+        // (a second outer role walked in between brings up to 1 MB past it).
+        // Of 524 streamed calls 48 became 1.02 to 1.28 times as fast, none less
+        // than 0.97; 256 agents, 15 x 32 x 24 x 6 states, 8 steps, VMP: 4.52 ->
+        // 3.58 ms (4.09 by the kernels of agent.hip).
+        s.flip = s.per > 1 && s.n[kO2] > 1 && s.s[kP] < s.s[kO2];
         s.parts = div_up(s.n[kP], s.per);
         s.lane0 = (int)lanes;
         lanes += (int64_t)s.na * s.nb * s.parts;
@@ -643,6 +651,12 @@ bool staged_is_better(int b, int threads, bool staged)
     return staged && div_up(b, kCus) * (threads / 64) > kWavesFit;
 }
 
+// Whether some modality's walk is flipped.
+bool flips(const StreamedArgs &c)
+{
+    return std::any_of(c.mod, c.mod + c.a.M, [](const SMod &s) { return s.flip != 0; });
+}
+
 // The kernel and arguments of a call.
 struct Choice {
     Plan p;           // (streamed: lds and threads of it)
@@ -669,7 +683,7 @@ bool choose(const bi_model *m, int algo, int b, int T, bool staged, Choice &c)
     if (make_streamed(m, algo, T, c.sa, p.lds, p.threads) && !staged_is_better(b, p.threads, staged)) {
         c.a = &c.sa.a;
         c.args = &c.sa;
-        c.fn = vmp ? vmp_streamed() : mmp_streamed();
+        c.fn = vmp ? vmp_streamed(flips(c.sa)) : mmp_streamed(flips(c.sa));
         c.name = "agent_window_streamed";
         return true;
     }
@@ -685,8 +699,8 @@ bool describe_resident(const bi_model *m, int algo, int b, int T, bool staged, c
     static const char *tabs[] = {"packed", "once", "twice"};
     const Plan &p = c.p;
     if (c.a == &c.sa.a)
-        std::snprintf(buf, cap, "%s chunk=%d steps=%d tables=%s threads=%d lds=%zu", c.name, c.sa.chunk, c.sa.steps,
-                      tabs[c.a->tab], p.threads, p.lds);
+        std::snprintf(buf, cap, "%s chunk=%d steps=%d flip=%d tables=%s threads=%d lds=%zu", c.name, c.sa.chunk,
+                      c.sa.steps, (int)flips(c.sa), tabs[c.a->tab], p.threads, p.lds);
     else
         std::snprintf(buf, cap, "%s tile=%dx%d tables=%s passes=%s groups=%d threads=%d lds=%zu", c.name,
                       kShapes[p.shape].rb, kShapes[p.shape].cb,

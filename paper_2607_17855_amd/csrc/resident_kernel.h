@@ -36,8 +36,8 @@
 // What bounds them: the latency of a sweep's two phases.  One agent's filter of
 // 4 states (79 us for 128 sweeps) issues vector instructions in 27% of the
 // cycles; 4096 agents of 12 x 10 x 8 states, 20 steps, MMP (1.12 ms; 6 x 4
-// tiles, one workgroup of 13 waves to a compute unit) in 42%, with LDS at work in
-// 29% and waves waiting in 61% of their cycles.  Its tiles spill: 116 bytes a
+// tiles, one workgroup of 13 waves to a compute unit) in 44%, with LDS at work in
+// 27% and waves waiting in 61% of their cycles.  Its tiles spill: 116 bytes a
 // lane, 0.4 GB a call.
 #pragma once
 

@@ -48,6 +48,7 @@ struct SMod {
     int32_t s[kSRoles];        // element strides in the slice
     int32_t na, nb, parts, per, lane0;       // blocks along row and column, parts of the outer states, first lane
     int32_t slice, m;
+    int32_t flip;              // the lane's own outer states are walked innermost, not the second ones
     int64_t la, la_agent, ll;
 };
 
@@ -62,7 +63,8 @@ struct Block {
     double x[kBlk][kBlk];
 };
 
-template <int ALGO>
+// FLIP: some modality's walk is flipped.
+template <int ALGO, bool FLIP>
 __global__ __launch_bounds__(kStreamThreads) void streamed_kernel(StreamedArgs c)
 {
     using BT = std::conditional_t<ALGO == BI_ALGO_VMP, double, float>;
@@ -96,7 +98,10 @@ __global__ __launch_bounds__(kStreamThreads) void streamed_kernel(StreamedArgs c
     const int bb = rem % nb;
     rem /= nb;
     const int ab = rem % na, part = rem / na;
-    const int row = kBlk * ab, o_first = part * md.per, o_count = min(md.per, md.n[kP] - o_first), n2 = md.n[kO2];
+    // outer states walked: o_count of its own (the names in _p), each with the n2
+    // second ones (_2), or flipped the other way round
+    const int row = kBlk * ab, o_first = part * md.per;
+    int o_count = min(md.per, md.n[kP] - o_first), n2 = md.n[kO2];
     // the last column block reaches back over states of the one before (skip
     // of them, left out) so that its loads stay inside the row
     const int ncol = md.n[kCol], col = max(0, min(kBlk * bb, ncol - kBlk)), skip = kBlk * bb - col;
@@ -105,16 +110,33 @@ __global__ __launch_bounds__(kStreamThreads) void streamed_kernel(StreamedArgs c
     for (int i = 0; i < kBlk; ++i) ro[i] = min(row + i, md.n[kRow] - 1) * md.s[kRow] + col * md.s[kCol];
     const int s_col = md.s[kCol], last_col = ncol - 1 - col;   // (fewer than 4 columns: the last one repeats, at weight 0)
     const bool rows4 = ncol >= kBlk && s_col == 1;
-    const int sp = md.s[kP], s2 = md.s[kO2], m_obs = md.m, slice = md.slice;
+    int sp = md.s[kP], s2 = md.s[kO2];
+    const int m_obs = md.m, slice = md.slice;
+    const int first = o_first * sp;   // element offset of its first outer state
     const char *X = a.ll ? reinterpret_cast<const char *>(a.ll + (int64_t)agent * a.T * a.llpc + md.ll)
                          : a.base + md.la + (a.shared ? 0 : (int64_t)agent * md.la_agent * 8);
-    const int q_row = md.q[kRow] + row, q_col = md.q[kCol] + col, q_p = md.q[kP] + o_first, q_2 = md.q[kO2];
-    const int parts = md.parts, pitch_row = md.pitch[kRow], pitch_col = md.pitch[kCol], pitch_p = md.pitch[kP],
-              pitch_2 = md.pitch[kO2];
+    const int q_row = md.q[kRow] + row, q_col = md.q[kCol] + col;
+    int q_p = md.q[kP] + o_first, q_2 = md.q[kO2];
+    const int parts = md.parts, pitch_row = md.pitch[kRow], pitch_col = md.pitch[kCol];
+    int pitch_p = md.pitch[kP], pitch_2 = md.pitch[kO2];
     const int l_row = md.line[kRow] + row * pitch_row + (md.q[kRow] ? bb * parts + part : 0);
     const int l_col = md.line[kCol] + col * pitch_col + ab * parts + part;
-    const int l_p = md.line[kP] + o_first * pitch_p + (md.q[kP] ? ab * nb + bb : 0);
-    const int l_2 = md.line[kO2] + (md.q[kO2] ? (ab * nb + bb) * parts + part : 0);
+    int l_p = md.line[kP] + o_first * pitch_p + (md.q[kP] ? ab * nb + bb : 0);
+    int l_2 = md.line[kO2] + (md.q[kO2] ? (ab * nb + bb) * parts + part : 0);
+    bool share_2 = n2 > 1;   // (an absent second outer role has no share)
+    if (FLIP && md.flip) {
+        auto swap = [](int &x, int &y) {
+            const int t = x;
+            x = y;
+            y = t;
+        };
+        swap(o_count, n2);
+        swap(sp, s2);
+        swap(q_p, q_2);
+        swap(pitch_p, pitch_2);
+        swap(l_p, l_2);
+        share_2 = true;
+    }
 
     auto load = [&](Block &b, uint32_t at0) {
         if (rows4) {
@@ -138,7 +160,7 @@ __global__ __launch_bounds__(kStreamThreads) void streamed_kernel(StreamedArgs c
                 const int q = cur + t * a.pq, p = a.o_p + (t - c0) * a.pl;
                 const uint32_t at0 = (a.ll ? (uint32_t)t * (uint32_t)a.llpc
                                            : (uint32_t)obs[t * a.M + m_obs] * (uint32_t)slice) +
-                                     (uint32_t)(o_first * sp);
+                                     (uint32_t)first;
                 double wa[kBlk], wb[kBlk], z[kBlk], v[kBlk];
 #pragma unroll
                 for (int i = 0; i < kBlk; ++i) {
@@ -174,7 +196,7 @@ __global__ __launch_bounds__(kStreamThreads) void streamed_kernel(StreamedArgs c
                         z[i] = fma(w, r, z[i]);
                     }
                     yp = fma(y, w2, yp);
-                    if (n2 > 1) {
+                    if (share_2) {
                         const int l = p + l_2 + o2 * pitch_2;
                         smem[l] = o ? fma(y, wp, smem[l]) : y * wp;
                     }
@@ -243,8 +265,8 @@ __global__ __launch_bounds__(kStreamThreads) void streamed_kernel(StreamedArgs c
     }
 }
 
-const void *vmp_streamed();
-const void *mmp_streamed();
+const void *vmp_streamed(bool flip);
+const void *mmp_streamed(bool flip);
 
 }  // namespace res
 }  // namespace bi

@@ -4,8 +4,15 @@
 namespace bi {
 namespace res {
 
-const void *vmp_streamed() { return (const void *)streamed_kernel<BI_ALGO_VMP>; }
-const void *mmp_streamed() { return (const void *)streamed_kernel<BI_ALGO_MMP>; }
+const void *vmp_streamed(bool flip)
+{
+    return flip ? (const void *)streamed_kernel<BI_ALGO_VMP, true> : (const void *)streamed_kernel<BI_ALGO_VMP, false>;
+}
+
+const void *mmp_streamed(bool flip)
+{
+    return flip ? (const void *)streamed_kernel<BI_ALGO_MMP, true> : (const void *)streamed_kernel<BI_ALGO_MMP, false>;
+}
 
 }  // namespace res
 }  // namespace bi

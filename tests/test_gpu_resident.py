@@ -70,6 +70,8 @@ STREAMED = {
     "streamed_steps": ([25, 32], [3, 2], [3, 4], [[0, 1], [1]], 2, 28, True),
     "streamed_tables": ([32, 31, 30], [5, 5, 2], [2], [[0, 1, 2]], 2, 3, False),
     "streamed_no_list": ([6, 32, 31, 29], [2, 1, 1, 2], [2], [[1, 2]], 3, 24, False),
+    # a list whose walk is flipped beside one without outer roles
+    "flipped_walk": ([15, 32, 25, 6], [3, 2, 1, 2], [3, 2], [[0, 1, 2, 3], [1]], 2, 6, True),
 }
 
 
