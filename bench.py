@@ -806,7 +806,7 @@ def bench_agent(args, bi, synth, torch, dev):
     # profiles/traffic_agent.json while the kernel sources are unchanged).  The
     # headline roofline is the one the kernel is closer to.
     alg_bytes = nb * w.b * t_launch * (1 if merged else w.iters)
-    tr = load_agent_traffic().get(args.workload)
+    tr = None if soft_np is not None else load_agent_traffic().get(args.workload)   # (counted with outcomes)
     hbm = tr["hbm_bytes_per_launch"] if tr and tr.get("kernel_source_sha") == source_sha(*sources) else None
     gbps = alg_bytes / (avg_ms / 1e3) / 1e9
     out["roofline_all"] = {
