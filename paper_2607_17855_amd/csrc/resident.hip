@@ -439,17 +439,20 @@ bool plan_shape(const bi_model *m, int algo, int b, int T, const Args &base, con
     // unit busy for 5 / 4 cycles each (4 SIMDs, 4 cycles for a wave's fp64
     // instruction, some of them idle), one wave's chain of them takes 10 each and
     // the barriers and LDS round trips 1000; as many workgroups as fit share
-    // a compute unit.  On the shapes tried the order of the estimates is that
-    // of the measured times within 5% (8 x 6 states, 1024 agents, VMP: 4 x 2
-    // tiles 36 us, 1 x 1 59 us; 12 x 10 x 8 states, 4096 agents, MMP: 6 x 4
-    // tiles 1.11 ms, 12 x 4 1.26 ms, 12 x 5 1.48 ms).
+    // a compute unit (8 x 6 states, 1024 agents, VMP: 4 x 2 tiles 36 us, 1 x 1
+    // 59 us; 12 x 10 x 8 states, 4096 agents, MMP: 6 x 4 tiles 1.11 ms, 12 x 4
+    // 1.26 ms, 12 x 5 1.48 ms).  The order of the estimates is not always that
+    // of the times: on 785 drawn calls the next shape was more than 5% faster
+    // 117 times, more than 20% 14 times, 0.38 of the time at the extreme (a
+    // filter on 2 x 2 tiles that 4 x 4 suit better).
     const int nmax = *std::max_element(m->n.begin(), m->n.end()), p = rb * cb;
     const double ic = 2.0 * p + 4.0 * (rb + cb) + 20.0;
     const double is = 160.0 + 2.0 * longest + (fpi ? 0.0 : (a.tab == kBoth ? 5.0 : a.tab == kOnce ? 8.0 : 16.0) * nmax) + 2.0 * nmax;
     const int regs = p <= 4 ? 80 : p <= 8 ? 96 : p <= 24 ? 128 : p <= 32 ? 200 : 256;
     const int fit = std::max(1, std::min(4 * (512 / regs) / waves, (int)(kLds / out.lds)));
     const int side = std::min(fit, div_up(b, kCus));   // workgroups side by side on a compute unit
-    const double issue = 1.25 * (cw * ic + units * is + trans) * (p > 48 ? 1.2 : 1.0);   // (the largest tiles spill)
+    // (12 x 5 and 8 x 8 spill 58 to 74 registers; 6 x 4, with 25 to 29, is not charged)
+    const double issue = 1.25 * (cw * ic + units * is + trans) * (p > 48 ? 1.2 : 1.0);
     const double chain = 10.0 * (ic + div_up(units, waves) * is + trans / waves) + (coupled ? 2000.0 : 1000.0);
     out.cost = std::max(side * issue, chain) * div_up(b, kCus * side);
     return true;
